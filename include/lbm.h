@@ -113,7 +113,7 @@ int lbm_create(int nx, int ny, int precision, int with_polish, void *workspace,
  * place).
  * Workspace: lbm_workspace_bytes_inplace (0 for invalid sizes) runs one step
  * per launch.  Temporal blocking in place (up to k = 2..8 steps per launch
- * through the register wavefront, LBM_FUSED_WAVEFRONT) needs room for copies
+ * through the wavefront, LBM_FUSED_WAVEFRONT) needs room for copies
  * of the columns and rows that neighbouring waves overwrite during a launch:
  * a ring of columns per strip and 2 x depth rows per segment, taken by a short
  * copy launch before each blocked launch.  lbm_workspace_bytes_inplace_blocked
@@ -346,10 +346,14 @@ int lbm_set_tile(lbm_solver *s, int bx_log2, int rows_per_thread, int blocks_per
 
 /* Temporal blocking: with steps_per_launch = k in 2..8, plain steps run k at a
  * time through one fused kernel, so populations cross HBM once per k steps.
- * Results are identical to single steps.  Residual-check steps, remainders
- * and the general-rates variant run one step per launch (with the tile kernel
- * a check rides on the last fused launch).  Overrides the tile shape of
- * lbm_set_tile while active.  Default by storage type and size: FP32 and FP16
+ * Results are identical to single steps.  A residual check rides on a fused
+ * tile launch.  General rates run through the wavefront (two buffers, without
+ * stochastic rounding; one step per launch otherwise).  Overrides the tile
+ * shape of lbm_set_tile while active.  While neither this nor
+ * lbm_set_fused_kernel nor lbm_set_tile_rows has been called, the lattices
+ * whose default is the wavefront, and general rates, run at the library's own
+ * depth (twelve steps per launch for FP64 and FP32, eight for FP16) and
+ * segment height.  Default by storage type and size: FP32 and FP16
  * 8 above 2^17 sites, else 4; FP64 5 below 458752 sites (the tile kernel),
  * else 8 (the wavefront; also after a polish switch).  The fused kernel follows the default of
  * lbm_set_fused_kernel for k until the caller picks one.  In place: the
@@ -376,12 +380,13 @@ enum lbm_fused_kernel {
      * 16 (8 for k <= 4 on lattices of up to 2^21 sites); FP16 12 for k <= 4,
      * 16 above. */
     LBM_FUSED_TILE = 0,
-    /* Register wavefront: a wave owns a strip of columns (one per lane, or
-     * two per lane for FP32/FP16 on even widths) with a ring of k columns per
-     * side (with two per lane: 4 for k <= 4, k rounded up to even above) and
-     * marches along y through segments of `segment_rows` rows, keeping the
-     * rows of every intermediate step that the next one still reads in
-     * registers (x neighbours through cross-lane moves); no LDS. */
+    /* Wavefront: a workgroup owns a strip of columns (two waves side by side
+     * with one column per lane, or one wave with two per lane for FP32/FP16 on
+     * even widths) with a ring of k columns per side (with two per lane: 4 for
+     * k <= 4, k rounded up to even above) and marches along y through segments
+     * of `segment_rows` rows; its waves are a pipeline over the k steps, each
+     * keeping the rows of two or three of them in registers (x neighbours
+     * through cross-lane moves) and handing rows on through LDS. */
     LBM_FUSED_WAVEFRONT = 1
 };
 
@@ -415,13 +420,16 @@ int lbm_set_stochastic_rounding(lbm_solver *s, int on, unsigned int seed);
 /* Current launch configuration of plain steps: out[0] steps per launch;
  * out[1] the fused kernel (LBM_FUSED_TILE, LBM_FUSED_WAVEFRONT, or -1 for one
  * step per launch); out[2] its tile rows (tile), segment rows (wavefront) or
- * rows per thread (one step per launch); out[3] threads per workgroup.
+ * rows per thread (one step per launch); out[3] threads per workgroup (of the
+ * wavefront: 256, four waves).  This is the shape that the lbm_set_* calls
+ * start from and change; while none has been called, the wavefront runs at the
+ * library's own depth and segment height instead (lbm_set_time_blocking), with
+ * the threads its depth needs.
  * out is a host array of 4 ints.  Errors: LBM_E_ARG. */
 int lbm_get_launch_config(const lbm_solver *s, int out[4]);
 
-/* Columns per lane of the register wavefront when plain steps run through it
- * (1 or 2: a wave's strip is 64 or 128 columns, of which 2 x ring are
- * recomputed neighbours), 0 otherwise.  Errors: LBM_E_ARG. */
+/* Columns per lane of the wavefront when the current launch configuration has
+ * it (1 or 2), 0 otherwise.  Errors: LBM_E_ARG. */
 int lbm_get_wave_columns(const lbm_solver *s);
 
 /* Diagnostic: nsteps of streaming alone (no collision), for bit-exact checks
@@ -437,7 +445,7 @@ const char *lbm_last_error(const lbm_solver *s);
 /* together, one persistent launch per step over a (lattice, tile) work list. */
 /* ------------------------------------------------------------------------ */
 /* Plain fused steps of some lattices run through a wavefront launch over a
- * list of their (lattice, strip, segment) waves, one column per lane, beside
+ * list of their (lattice, strip, segment) workgroups, one column per lane, beside
  * the tile launch of the others.  By default (see
  * lbm_batch_set_wavefront_sites) these are, per storage type, all of its
  * lattices once they hold at least 2^22 (FP64), 2^23 (FP32) or 2^24 (FP16)
@@ -522,7 +530,8 @@ int lbm_batch_set_tile(lbm_batch *b, int bx_log2, int rows_per_thread, int block
 
 /* Temporal blocking for all lattices of the batch (see lbm_set_time_blocking,
  * 1..8).  Until set, a storage type with lattices on the wavefront list runs
- * eight steps per launch, and otherwise takes the tile kernel's default for
+ * eight steps per launch (FP64 and FP32 twelve when all of its lattices are on
+ * it), and otherwise takes the tile kernel's default for
  * the total sites of its lattices in the batch (FP64 5, FP32 / FP16 8 above
  * 2^17 sites).  Errors: LBM_E_ARG. */
 int lbm_batch_set_time_blocking(lbm_batch *b, int steps_per_launch);

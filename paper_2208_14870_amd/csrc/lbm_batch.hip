@@ -221,12 +221,12 @@ struct lbm_batch {
     unsigned grid_tile_for(int prec) const {
         return bucket(range_tile_host[prec][1] - range_tile_host[prec][0]);
     }
-    // workgroups of four waves for the wavefront list (power-of-two buckets)
+    // workgroups of the wavefront list (power-of-two buckets)
     unsigned grid_wave_for(int prec) const {
         const int n = wrange_host[prec][1] - wrange_host[prec][0];
         if (n <= 0) return 0;
         unsigned g = 8;
-        while (g * (kBlock / kWave) < (unsigned)n) g <<= 1;
+        while (g < (unsigned)n) g <<= 1;
         return g;
     }
 
@@ -266,16 +266,17 @@ struct lbm_batch {
         }
         for (int p = 0; p < 3; ++p) {
             long long sites = 0;
-            bool large = false;  // a lattice on the wavefront list: eight steps per launch
+            bool large = false, small = false;  // a lattice on / not on the wavefront list
             for (int i = 0; i < max_slots; ++i)
                 if (slots[i].active && slots[i].L.prec == p) sites += slots[i].L.N;
             wave_all[p] = sites >= batch_wave_total(p);
             for (int i = 0; i < max_slots; ++i)
                 if (slots[i].active && slots[i].L.prec == p)
-                    large = large || on_wave_list(p, slots[i].L.N);
-            // the wavefront runs eight steps best (FP64 4 x 1500^2 in a batch:
-            // 116 GLUPS at the tile's five), and its lattices carry the work
-            if (tb_auto[p]) tb[p] = large ? 8 : default_time_blocking(p, sites, true);
+                    (on_wave_list(p, slots[i].L.N) ? large : small) = true;
+            // the wavefront runs its own depth best, and its lattices carry the
+            // work; beside lattices on the tile kernel the eight steps that both run
+            if (tb_auto[p])
+                tb[p] = !large ? default_time_blocking(p, sites, true) : small ? 8 : wave_depth(p);
             th[p] = fused_th(p, tb[p], sites);
         }
         // Per precision: the tile work list of every lattice (single steps and
@@ -286,8 +287,8 @@ struct lbm_batch {
         for (int p = 0; p < 3; ++p) {
             range_host[p][0] = (int)total;
             wrange_host[p][0] = (int)h_witems.size();
-            long long wave_cols_rows = 0;  // strips x rows of its wavefront lattices
-            const int w = tb[p] >= 2 ? wave_width_of(tb[p], 1) : 0;
+            int wave_ny = 0;  // rows of its tallest wavefront lattice
+            const int w = tb[p] >= 2 ? wave_out(tb[p], 1, is_half(p)) : 0;
             for (int pass = 0; pass < 2; ++pass) {
                 for (int i = 0; i < max_slots; ++i) {
                     BSlot& s = slots[i];
@@ -302,7 +303,7 @@ struct lbm_batch {
                     s.count = s.L.nitems();
                     total += s.count;
                     h_rows[nrows++] = SlotRow{i, s.first, s.L.tiles_x(), s.count};
-                    if (s.wave) wave_cols_rows += (long long)((s.L.nx + w - 1) / w) * s.L.ny;
+                    if (s.wave) wave_ny = std::max(wave_ny, s.L.ny);
                 }
                 if (pass == 0) {
                     range_tile_host[p][0] = range_host[p][0];
@@ -310,9 +311,16 @@ struct lbm_batch {
                 }
             }
             range_host[p][1] = (int)total;
-            // segments as long as leaves one wave per SIMD over the list, 16..128 rows
-            const int hs = (int)std::min<long long>(
-                128, std::max<long long>(16, (wave_cols_rows + 4LL * cus - 1) / (4LL * cus)));
+            auto groups = [&](int hs) {
+                long long n = 0;
+                for (const BSlot& s : slots)
+                    if (s.active && s.L.prec == p && s.wave)
+                        n += (long long)((s.L.nx + w - 1) / w) * ((s.L.ny + hs - 1) / hs);
+                return n;
+            };
+            const int hs = wave_ny ? wave_segment_rows(tb[p], cus, wave_blocks_per_cu(p, tb[p], 1),
+                                                       16, wave_ny, groups)
+                                   : 1;
             for (int i = 0; i < max_slots && w > 0; ++i) {
                 const BSlot& s = slots[i];
                 if (!s.active || s.L.prec != p || !s.wave) continue;
@@ -378,30 +386,36 @@ struct lbm_batch {
     // rows per thread of the tiles of one precision's lattices
     int eff_vy(int prec) const { return tb[prec] >= 2 ? th[prec] / 4 : vy; }
 
-    // Whether a remainder of r < tb[p] plain steps runs as one fused launch.
-    bool fused_rest(int p, long long r) const {
-        return tb[p] >= 2 && r >= 2 && stepN_supported(p, (int)r, th[p]);
+    // Steps of the next launch of precision p when `rem` plain steps are left: a
+    // full launch, else the remainder as one shorter launch where kernels exist
+    // for it (up to eight steps; 9..11 as two launches), else a single step.
+    int next_span(int p, long long rem) const {
+        if (tb[p] < 2) return 1;
+        if (rem >= tb[p]) return tb[p];
+        if (rem > 8) return rem == 9 ? 5 : 8;
+        return (rem >= 2 && stepN_supported(p, (int)rem, th[p])) ? (int)rem : 1;
     }
 
-    // Launches of np plain steps of precision p: groups of tb[p] through the
-    // fused kernel, the remainder as one shorter fused launch or single steps.
+    // Launches of np plain steps of precision p.
     long long plain_launches(int p, long long np) const {
-        if (tb[p] < 2) return np;
-        const long long r = np % tb[p];
-        return np / tb[p] + (fused_rest(p, r) ? 1 : r);
+        const long long d = std::max(1, tb[p]);
+        long long n = np / d;
+        for (long long rem = np % d; rem > 0; ++n) rem -= next_span(p, rem);
+        return n;
     }
 
     // A checked sequence of n steps of precision p: `plain` steps through the
     // ordinary launches, then one fused launch of `span` steps whose last two
     // steps form the residual check (span 0: a write-u step and a check step,
     // one step per launch).  The span makes the plain part whole launches: the
-    // remainder of n (at least 2), else a full launch.
+    // remainder of n (at least 2), else a full launch of up to eight steps, four
+    // after launches of twelve.
     void check_plan(int p, long long n, long long& plain, int& span) const {
         plain = n - 2;
         span = 0;
         if (tb[p] < 2) return;
         const long long r = n % tb[p];
-        const long long k = (r >= 2) ? r : tb[p];
+        const long long k = (r >= 2 && r <= 8) ? r : tb[p] <= 8 ? tb[p] : 4;
         if (k > n || !stepN_supported(p, (int)k, th[p])) return;
         plain = n - k;
         span = (int)k;
@@ -438,17 +452,13 @@ struct lbm_batch {
                     r = launch_wave_list(p, ns, d_desc, d_witems, d_wrange + 2 * p, nw, flip, gw, st);
                 return r;
             };
-            if (tb[p] >= 2) {
-                for (; i + tb[p] <= np && e == hipSuccess; i += tb[p], ++ph)
-                    e = fused(tb[p], (int)(ph & 1));
-                if (e == hipSuccess && fused_rest(p, np - i)) {
-                    e = fused((int)(np - i), (int)(ph & 1));
-                    ++ph;
-                    i = np;
-                }
+            for (; i < np && e == hipSuccess; ++ph) {
+                const int k = next_span(p, np - i);
+                e = k > 1 ? fused(k, (int)(ph & 1))
+                          : launch_step(p, kPlain, false, eff_vy(p), kLayPull, g, st,
+                                        args(p, (int)(ph & 1)));
+                i += k;
             }
-            for (; i < np && e == hipSuccess; ++i, ++ph)
-                e = launch_step(p, kPlain, false, eff_vy(p), kLayPull, g, st, args(p, (int)(ph & 1)));
             if (check && e == hipSuccess && span) {
                 e = launch_stepN(p, span, th[p], g, st, args(p, (int)(ph & 1)), true);
             } else if (check && e == hipSuccess) {
@@ -516,7 +526,7 @@ int lbm_batch_create(int max_slots, void* arena, size_t arena_bytes, void* strea
     b->d_rows = reinterpret_cast<SlotRow*>(take((max_slots + 5) * sizeof(SlotRow)));
     b->d_red = reinterpret_cast<double*>(take((kErrBlocks * 8 + 16) * sizeof(double)));
     b->d_items = reinterpret_cast<Item*>(take(b->cap_items * sizeof(Item)));
-    // wavefront items: no more than tile items (a wave covers at least 48 x 16 sites)
+    // wavefront items: no more than tile items (one covers at least 48 x 16 sites)
     b->d_witems = reinterpret_cast<WaveItem*>(take(b->cap_items * sizeof(WaveItem)));
     b->d_partial = reinterpret_cast<double*>(take(b->cap_items * 3 * sizeof(double)));
     if (off > arena_bytes) {

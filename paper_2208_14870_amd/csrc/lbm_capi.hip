@@ -89,6 +89,8 @@ struct lbm_solver {
     double r_switch = 0.0;
     int blocks_per_cu = 0;  // 0: one workgroup per tile; k: persistent k per CU
     bool fused_auto = true;  // fused kernel not chosen by the caller: follows the default
+    bool depth_auto = true;  // nor the steps per launch
+    PlainPlan plan;          // what plain steps run through (make_plan)
     // steps per launch of the one-workgroup solve of small lattices (0: off)
     long long small_budget = 65536;
     // divergence guard of lbm_solve_to_tol: rises of the residual in a row (0: off)
@@ -116,11 +118,61 @@ struct lbm_solver {
         graphs.clear();
     }
 
+    // The launches of plain steps.  Left to the library, large lattices and all
+    // lattices with free rates run through the wavefront at its own depth and
+    // segment height; a depth, kernel or height that the caller chose is taken
+    // as given.
+    void make_plan() {
+        plan = PlainPlan();
+        const int prec = L.prec;
+        if (L.inplace) {
+            if (!L.ip_blocked()) return;
+            plan.wave = true;
+            plan.ns = L.tb;
+            plan.v = L.wave_v;
+            // the nominal height or longer (fewer row copies; the room for the
+            // halo copies is that of the nominal height)
+            const int w = wave_out(plan.ns, plan.v, is_half(prec));
+            const long long strips = (L.nx + w - 1) / w;
+            plan.hs = fused_auto ? wave_segment_rows(plan.ns, cus, wave_blocks_per_cu(prec, plan.ns, plan.v),
+                                                     L.wave_hs, L.ny,
+                                                     [&](int hs) { return strips * ((L.ny + hs - 1) / hs); })
+                                 : L.wave_hs;
+            return;
+        }
+        const bool gen = L.general();
+        if (L.tb < 2 || (gen ? L.sr_on() || (!fused_auto && L.wave_hs == 0) : !L.fused())) return;
+        const bool chosen = !fused_auto || !depth_auto || L.th_user > 0;
+        if (!gen && (chosen ? L.wave_hs == 0 : !wave_auto(prec, L.N) && L.tile_fits())) return;
+        plan.wave = true;
+        plan.ns = depth_auto && fused_auto ? wave_depth(prec) : L.tb;
+        plan.v = wave_cols(prec, plan.ns, L.nx, L.ny);
+        const int w = wave_out(plan.ns, plan.v, is_half(prec));
+        const long long strips = (L.nx + w - 1) / w;
+        plan.hs = fused_auto ? wave_segment_rows(plan.ns, cus, wave_blocks_per_cu(prec, plan.ns, plan.v),
+                                                 4, L.ny,
+                                                 [&](int hs) { return strips * ((L.ny + hs - 1) / hs); })
+                             : L.wave_hs;
+    }
+
+    // Steps per full launch of plain steps, and of the next launch when `rem`
+    // steps are left: a full launch, else the remainder as one shorter launch
+    // where a kernel exists for it (the wavefront: up to eight steps, 9..11 as
+    // two launches), else a single step.
+    int depth() const { return plan.wave ? plan.ns : (L.fused() ? L.tb : 1); }
+    int next_span(long long rem) const {
+        const int d = depth();
+        if (rem >= d) return d;
+        if (plan.wave) return rem <= 8 ? (int)std::max(1LL, rem) : (rem == 9 ? 5 : 8);
+        return (rem >= 2 && stepN_supported(L.prec, (int)rem, L.th)) ? (int)rem : 1;
+    }
+
     // Rewrite descriptor + work list (after any change of layout or parameters).
     int sync_desc() {
         // keep the state buffer: fold the phase parity into cur
         L.cur = sel();
         phase = 0;
+        make_plan();
         SlotDesc d = L.desc();
         d.sr_step = (unsigned)steps;  // stochastic rounding: steps enqueued before
         nitems = L.nitems();
@@ -132,7 +184,7 @@ struct lbm_solver {
         hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, stream, d_count, nitems);
         hipLaunchKernelGGL(k_build_items, dim3(blocks_for(nitems)), dim3(kBlock), 0, stream,
                            d_items, 0, 0, d.tiles_x, nitems,
-                           (L.fused() && L.wave_hs == 0) ? kItemBand : 0);
+                           (L.fused() && !plan.wave) ? kItemBand : 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "descriptor upload");
         unsigned g = (unsigned)((nitems + 7) / 8 * 8);
@@ -168,12 +220,12 @@ struct lbm_solver {
         return e;
     }
 
-    // One fused launch of ns steps (L.tb, or a shorter remainder).
+    // One fused launch of ns steps (a full launch, or a shorter remainder).
     hipError_t enqueue_fused(int ns, hipStream_t st, long long& ph) {
         hipError_t e =
-            L.wave_hs > 0
-                ? launch_wave(L.prec, ns, L.wave_v, L.nx, L.ny, L.wave_hs, d_desc, (int)(ph & 1), st,
-                              L.sr_on())
+            plan.wave
+                ? launch_wave(L.prec, ns, plan.v, L.nx, L.ny, plan.hs, d_desc, (int)(ph & 1), st,
+                              L.sr_on(), L.general())
                 : launch_stepN(L.prec, ns, L.th, grid, st, launch_args((int)(ph & 1)), false,
                                L.sr_on());
         ++ph;  // one buffer flip for ns steps
@@ -185,7 +237,7 @@ struct lbm_solver {
     // from kLayNatural, even from kLaySwapped); the layout flips per step, so
     // the launch parity advances by ns.
     hipError_t enqueue_fused_ip(int ns, hipStream_t st, long long& ph) {
-        hipError_t e = launch_wave_inplace(L.prec, ns, L.wave_v, L.nx, L.ny, L.wave_hs, d_desc,
+        hipError_t e = launch_wave_inplace(L.prec, ns, plan.v, L.nx, L.ny, plan.hs, d_desc,
                                            (int)(ph & 1), L.halo, st);
         ph += ns;
         return e;
@@ -210,12 +262,6 @@ struct lbm_solver {
         return e;
     }
 
-    // Whether a remainder of r < L.tb plain steps runs as one fused launch.
-    bool fused_rest(long long r) const {
-        return L.fused() && r >= 2 &&
-               (L.wave_hs > 0 ? r <= 8 : stepN_supported(L.prec, (int)r, L.th));
-    }
-
     hipError_t enqueue_finalize(hipStream_t st) {
         FinalizeLaunch F;
         F.first = d_first;
@@ -229,27 +275,34 @@ struct lbm_solver {
 
     // Steps per captured graph of plain steps: about 64, whole launches.
     long long graph_chunk() const {
-        return L.fused() ? std::max(1, 64 / L.tb) * (long long)L.tb : 64;
+        return L.inplace ? 64 : std::max(1, 64 / depth()) * (long long)depth();
     }
 
-    // Launches of np plain steps: groups of L.tb through the fused kernel when
-    // enabled, the remainder as one shorter fused launch where a kernel exists
-    // for it, else one per launch.
+    // Launches of np plain steps (two buffers), see next_span.
     long long plain_launches(long long np) const {
-        if (!L.fused()) return np;
-        const long long r = np % L.tb;
-        return np / L.tb + (fused_rest(r) ? 1 : r);
+        if (L.inplace) return np;
+        const int d = depth();
+        long long n = np / d;
+        for (long long rem = np % d; rem > 0; ++n) rem -= next_span(rem);
+        return n;
     }
 
     // Steps of the fused launch that ends a sequence of n steps whose last two
-    // are a write-u step and a check step (two buffers, LDS tile kernel): the
-    // remainder of n (at least 2), else a full launch, so that the plain part
-    // is whole launches; 0 when that launch has no kernel (the two steps then
-    // run one per launch).
+    // are a write-u step and a check step (two buffers, LDS tile kernel over the
+    // tile work list): with plain launches of d steps the remainder of n, so
+    // that the plain part is whole launches, at least 2 (a full launch when n is
+    // a multiple); after wavefront launches, which are faster per step, two to
+    // five, such that what they leave is one wavefront launch or none.  0 when
+    // that launch has no kernel (the two steps then run one per launch; FP64
+    // 1023 x 770: 61 us for the two, 105 for a tile launch of eight that carries
+    // them, 45 for one of four).
     int check_span(long long n) const {
-        if (!L.fused() || L.wave_hs > 0 || L.inplace) return 0;
-        const long long r = n % L.tb;
-        const long long k = (r >= 2) ? r : L.tb;
+        if (!L.fused() || L.inplace || !L.tile_fits()) return 0;
+        const int d = depth();
+        const long long r = n % d;
+        long long k = r >= 2 ? r : d;
+        if (plan.wave) k = (r >= 2 && r <= 4) ? r : r == 1 ? 5 : r == 5 ? 3 : 4;
+        while (plan.wave && k > 2 && (k > n || !stepN_supported(L.prec, (int)k, L.th))) --k;
         return (k <= n && stepN_supported(L.prec, (int)k, L.th)) ? (int)k : 0;
     }
 
@@ -263,18 +316,15 @@ struct lbm_solver {
         hipError_t e = hipSuccess;
         const int span = (writeu && check) ? check_span(nplain + 2) : 0;
         const long long np = span ? nplain + 2 - span : nplain;
-        long long i = 0;
-        if (L.fused()) {
-            for (; i + L.tb <= np && e == hipSuccess; i += L.tb) e = enqueue_fused(L.tb, st, ph);
-            if (e == hipSuccess && fused_rest(np - i)) {
-                e = enqueue_fused((int)(np - i), st, ph);
-                i = np;
-            }
-        } else if (L.ip_blocked()) {
+        if (L.ip_blocked()) {
             e = enqueue_ip(np, st, ph);
-            i = np;
+        } else {
+            for (long long i = 0; i < np && e == hipSuccess;) {
+                const int k = L.inplace ? 1 : next_span(np - i);
+                e = k > 1 ? enqueue_fused(k, st, ph) : enqueue_one(kPlain, st, ph);
+                i += k;
+            }
         }
-        for (; i < np && e == hipSuccess; ++i) e = enqueue_one(kPlain, st, ph);
         if (e == hipSuccess && span) {
             e = launch_stepN(L.prec, span, L.th, grid, st, launch_args((int)(ph & 1)), true,
                              L.sr_on());
@@ -338,10 +388,9 @@ struct lbm_solver {
         const int flip0 = (int)(phase & 1);
         const int kind = (writeu ? 1 : 0) | (check ? 2 : 0) | (L.general() ? 4 : 0) |
                          (L.inplace ? 8 : 0) | (L.sr_on() ? 16 : 0);
-        const int fused = L.fused() ? L.tb | (L.th << 4)
-                                    : (L.ip_blocked() ? L.tb | (L.wave_v << 8) | (1 << 12) : 0);
-        auto key = std::make_tuple(nplain, kind, flip0 ^ (L.cur << 1), L.prec, L.eff_vy(), fused,
-                                   (L.fused() || L.ip_blocked()) ? L.wave_hs : 0, grid);
+        const int shape = depth() | (L.th << 4) | (plan.wave ? 1 << 10 | plan.v << 11 : 0);
+        auto key = std::make_tuple(nplain, kind, flip0 ^ (L.cur << 1), L.prec, L.eff_vy(), shape,
+                                   plan.wave ? plan.hs : 0, grid);
         auto it = graphs.find(key);
         hipError_t e;
         if (it == graphs.end()) {
@@ -692,6 +741,7 @@ int lbm_set_time_blocking(lbm_solver* s, int steps_per_launch) {
     if (steps_per_launch < 1 || steps_per_launch > 8)
         return s->fail(LBM_E_ARG, "set_time_blocking: steps_per_launch must be in 1..8");
     Lattice& L = s->L;
+    s->depth_auto = false;
     if (L.inplace) {
         if (steps_per_launch >= 2) {
             const int v = ip_wave_cols(L.prec, steps_per_launch, L.nx);
@@ -856,6 +906,8 @@ int promote_solver(lbm_solver* s) {
     default_tile(LBM_FP64, L.nx, L.ny, L.bx_log2, L.vy);
     L.tb = default_time_blocking(LBM_FP64, L.N);
     L.th = fused_th(LBM_FP64, L.tb, L.N);
+    L.th_user = 0;
+    s->depth_auto = true;
     const FusedChoice fc = default_fused(LBM_FP64, L.tb, L.nx, L.ny, s->cus, !L.tile_fits());
     L.wave_hs = fc.wave_hs;
     L.wave_v = fc.wave_v;

@@ -219,12 +219,12 @@ __device__ __forceinline__ void bared_u(const C f[8], C gx, C gy, C& ux, C& uy) 
     uy = ((f[1] - f[3]) + (p + q)) + C(0.5) * gy;
 }
 
-// The collision with the force given as its half and quarter (hgx = gx/2,
-// qgx = hgx/2, formed by the caller with exactly these two products, so that
-// kernels that keep them per site across steps round as collide() does).
+// The collision with the force given as its quarter (qgx = gx/4, an exact
+// product): the half force that the first moments need is 2 qgx, taken inside
+// a fused multiply-add whose product is exact, so ux rounds as m10 + gx/2
+// does.  Kernels keep one value per force component and site instead of two.
 template <typename C, bool GENERAL>
-__device__ __forceinline__ void collide_h(C f[8], C hgx, C hgy, C qgx, C qgy, const Coef<C>& k,
-                                          C& ux, C& uy) {
+__device__ __forceinline__ void collide_q(C f[8], C qgx, C qgy, const Coef<C>& k, C& ux, C& uy) {
 #pragma clang fp contract(off)
     const C p = f[4] - f[6];   // f5 - f7
     const C q = f[5] - f[7];   // f6 - f8
@@ -239,8 +239,8 @@ __device__ __forceinline__ void collide_h(C f[8], C hgx, C hgy, C qgx, C qgy, co
     const C m11 = sac - sbd;
     const C ms = fmac(C(2), sac + sbd, h13 + h24);  // (h13 + h24) + 2 (sac + sbd): 2x is exact
     const C md = h13 - h24;
-    ux = m10 + hgx;
-    uy = m01 + hgy;
+    ux = fmac(C(2), qgx, m10);  // m10 + gx/2: the product is exact
+    uy = fmac(C(2), qgy, m01);
     if constexpr (!GENERAL) {
         const C dd = k.cd * md;
         const C a = fmac(k.cs, ms, dd);
@@ -260,7 +260,7 @@ __device__ __forceinline__ void collide_h(C f[8], C hgx, C hgy, C qgx, C qgy, co
         f[7] = t2 - s;
     } else {
         const C m22 = sac + sbd;
-        const C s10 = ux + hgx, s01 = uy + hgy;
+        const C s10 = fmac(C(2), qgx, ux), s01 = fmac(C(2), qgy, uy);
         const C s11 = k.a11 * m11;
         const C sss = k.as * ms;
         const C sdd = k.ad * md;
@@ -284,8 +284,7 @@ __device__ __forceinline__ void collide_h(C f[8], C hgx, C hgy, C qgx, C qgy, co
 template <typename C, bool GENERAL>
 __device__ __forceinline__ void collide(C f[8], C gx, C gy, const Coef<C>& k, C& ux, C& uy) {
 #pragma clang fp contract(off)
-    const C hgx = C(0.5) * gx, hgy = C(0.5) * gy;
-    collide_h<C, GENERAL>(f, hgx, hgy, C(0.5) * hgx, C(0.5) * hgy, k, ux, uy);
+    collide_q<C, GENERAL>(f, C(0.25) * gx, C(0.25) * gy, k, ux, uy);
 }
 
 // ---------------------------------------------------------------------------

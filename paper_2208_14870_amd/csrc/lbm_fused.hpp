@@ -1,5 +1,5 @@
 // Temporal blocking through an LDS tile: several steps per launch,
-// bit-identical to single steps (the register wavefront is in lbm_wave.hpp).
+// bit-identical to single steps (the wavefront is in lbm_wave.hpp).
 #pragma once
 
 #include <type_traits>
@@ -211,23 +211,8 @@ __device__ __forceinline__ void stepN_load(const S* __restrict__ src,
     }
 }
 
-// Whether the tile kernel keeps the quarter force of every slot in registers
-// (FP32 / FP64: LDS, not registers, limits their workgroups per CU) or forms it
-// at each collision (half storage: four more registers per thread would cost a
-// workgroup per CU).  Either way it is the same product of the half force.
-template <typename S>
-constexpr bool kKeepQuarter = !std::is_same<S, __half>::value;
-
-// The quarter force of slot a for a collision.
-template <typename S, typename C>
-__device__ __forceinline__ C quarter(const C hq[][2], const C qg[][2], int a, int c) {
-#pragma clang fp contract(off)
-    if constexpr (kKeepQuarter<S>) return qg[a][c];
-    else return C(0.5) * hq[a][c];
-}
-
-// Scales the force of every slot and keeps its half (hg) and, where registers
-// allow, its quarter (qg): the products collide() forms, taken once per tile.
+// Scales the force of every slot and keeps its quarter (qg): the product
+// collide() forms, taken once per tile.
 // Collides and writes step 1 to LDS; up[a] receives u of the step (for a check
 // launch of two steps, u(n - 1)).
 template <typename S, int TH, int NS, int NT = kBlock>
@@ -236,7 +221,6 @@ __device__ __forceinline__ void stepN_collide1(typename Store<S>::C f[][8],
                                                const SlotGeo<TH, NS, NT>& geo,
                                                const typename Store<S>::C gx[],
                                                const typename Store<S>::C gy[],
-                                               typename Store<S>::C hg[][2],
                                                typename Store<S>::C qg[][2],
                                                typename Store<S>::C up[][2],
                                                const unsigned sid[], bool sr, unsigned sh) {
@@ -247,14 +231,9 @@ __device__ __forceinline__ void stepN_collide1(typename Store<S>::C f[][8],
 #pragma unroll
     for (int a = 0; a < NM; ++a) {
         const int e = (int)threadIdx.x + a * NT;
-        hg[a][0] = C(0.5) * (gx[a] * k.gscale);
-        hg[a][1] = C(0.5) * (gy[a] * k.gscale);
-        if constexpr (kKeepQuarter<S>) {
-            qg[a][0] = C(0.5) * hg[a][0];
-            qg[a][1] = C(0.5) * hg[a][1];
-        }
-        collide_h<C, false>(f[a], hg[a][0], hg[a][1], quarter<S>(hg, qg, a, 0),
-                            quarter<S>(hg, qg, a, 1), k, up[a][0], up[a][1]);
+        qg[a][0] = C(0.25) * (gx[a] * k.gscale);
+        qg[a][1] = C(0.25) * (gy[a] * k.gscale);
+        collide_q<C, false>(f[a], qg[a][0], qg[a][1], k, up[a][0], up[a][1]);
         if (geo.active(a, 0)) {
             if constexpr (std::is_same<S, __half>::value) {
                 if (sr) {
@@ -321,7 +300,6 @@ template <typename S, int TH, int NS, int NT = kBlock, int MODE = kPlain>
 __device__ __forceinline__ void stepN_rest(S* __restrict__ dst, long long plane, int nx, int ny,
                                            int x0, int y0, const Coef<typename Store<S>::C>& k,
                                            S* lds, const SlotGeo<TH, NS, NT>& geo,
-                                           const typename Store<S>::C hg[][2],
                                            const typename Store<S>::C qg[][2],
                                            typename Store<S>::C up[][2], double* u,
                                            double inv_scale, double* partial, double* red,
@@ -342,8 +320,7 @@ __device__ __forceinline__ void stepN_rest(S* __restrict__ dst, long long plane,
             if (geo.active(a, m)) {
                 C f[8], ux, uy;
                 lds_read<S, RW, RN>(lds, e, even, f);
-                collide_h<C, false>(f, hg[a][0], hg[a][1], quarter<S>(hg, qg, a, 0),
-                                    quarter<S>(hg, qg, a, 1), k, ux, uy);
+                collide_q<C, false>(f, qg[a][0], qg[a][1], k, ux, uy);
                 bool rounded = false;
                 if constexpr (std::is_same<S, __half>::value) {
                     if (sr) {
@@ -371,8 +348,7 @@ __device__ __forceinline__ void stepN_rest(S* __restrict__ dst, long long plane,
         if (geo.active(a, R) && x < nx && y < ny) {  // the tile, inside the lattice
             C f[8], ux, uy;
             lds_read<S, RW, RN>(lds, e, last_even, f);
-            collide_h<C, false>(f, hg[a][0], hg[a][1], quarter<S>(hg, qg, a, 0),
-                                quarter<S>(hg, qg, a, 1), k, ux, uy);
+            collide_q<C, false>(f, qg[a][0], qg[a][1], k, ux, uy);
             const unsigned sidx = (unsigned)y * (unsigned)nx + (unsigned)x;
             bool rounded = false;
             if constexpr (std::is_same<S, __half>::value) {
@@ -439,17 +415,17 @@ static __global__ __launch_bounds__(NT) void k_stepN(StepLaunch L) {
         Coef<C> k;
         k.load(d);
         const int x0 = item.tx * kTW, y0 = item.ty * TH;
-        C f[NM][8], gx[NM], gy[NM], hg[NM][2], qg[kKeepQuarter<S> ? NM : 1][2], up[NM][2];
+        C f[NM][8], gx[NM], gy[NM], qg[NM][2], up[NM][2];
         constexpr bool sr = SR && std::is_same<S, __half>::value;
         unsigned sid[sr ? NM : 1];  // site index per slot (stochastic rounding)
         stepN_load<S, TH, NS, NT, sr>(reinterpret_cast<const S*>(d.buf[sel]),
                                   reinterpret_cast<const C*>(d.g), d.plane, d.nx, d.ny, x0, y0,
                                   geo, f, gx, gy, sid);
-        stepN_collide1<S, TH, NS, NT>(f, k, lds, geo, gx, gy, hg, qg, up, sid, sr,
+        stepN_collide1<S, TH, NS, NT>(f, k, lds, geo, gx, gy, qg, up, sid, sr,
                                       sr ? sr_step_hash(d.sr_step, d.sr_seed) : 0u);
         __syncthreads();
         stepN_rest<S, TH, NS, NT, MODE>(reinterpret_cast<S*>(d.buf[sel ^ 1]), d.plane, d.nx, d.ny,
-                                        x0, y0, k, lds, geo, hg, qg, up, d.u, d.inv_scale,
+                                        x0, y0, k, lds, geo, qg, up, d.u, d.inv_scale,
                                         L.partial + 3 * it, red, sid, sr, d.sr_step, d.sr_seed);
     }
 }

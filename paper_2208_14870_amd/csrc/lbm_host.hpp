@@ -371,7 +371,8 @@ inline FusedChoice default_fused(int prec, int ns, int nx, int ny, int cus, bool
     const bool wave = beyond_tile || wave_by_default(prec, n);
     if (!wave || ns < 2) return c;
     c.wave_v = wave_cols(prec, ns, nx, ny);
-    const long long strips = (nx + wave_width_of(ns, c.wave_v) - 1) / wave_width_of(ns, c.wave_v);
+    const int w = kWave * c.wave_v - 2 * wave_ring_of(ns, c.wave_v);
+    const long long strips = (nx + w - 1) / w;
     // segments as long as one wave per SIMD allows (fewest halo rows with the
     // chip filled), 16..128 rows
     const long long per = std::max(1LL, 4LL * cus / strips);
@@ -389,7 +390,8 @@ inline int ip_wave_cols(int prec, int ns, int nx) {
     return (prec != LBM_FP64 && nx % 2 == 0 && (prec == LBM_FP32 || ns <= 4)) ? 2 : 1;
 }
 inline int ip_segment_rows(int ns, int v, int nx, int ny) {
-    const long long strips = (nx + wave_width_of(ns, v) - 1) / wave_width_of(ns, v);
+    const int w = kWave * v - 2 * wave_ring_of(ns, v);
+    const long long strips = (nx + w - 1) / w;
     int hs = 256;
     while (hs > 32 && strips * ((ny + hs - 1) / hs) < 4096) hs /= 2;
     return hs;
@@ -401,6 +403,48 @@ inline size_t ip_halo_bytes(int prec, int ns, int nx, int ny, int hs = 0) {
     return wave_halo_bytes(prec, ns, v, nx, ny, hs > 0 ? hs : ip_segment_rows(ns, v, nx, ny));
 }
 
+// What plain steps of a lattice run through when the caller leaves the choice to
+// the library: the wavefront (ns steps per launch, v columns per lane, segments
+// of hs rows), or the kernel of the nominal shape (Lattice::tb, th, wave_hs).
+struct PlainPlan {
+    bool wave = false;
+    int ns = 0, v = 1, hs = 0;
+};
+
+// Segment rows of a wavefront over `groups(hs)` workgroups, `per_cu` of which a
+// compute unit holds at a time: the height that finishes first.  A workgroup
+// runs hs rows and about 2 ns more for its halo; m workgroups that share a
+// compute unit take (a + m) / (a + 1) times as long as one of them, a = 2
+// (measured, FP32 1024^2 at eight steps: one workgroup per compute unit 0.37 us
+// per row, two 0.43, three 0.54), so long segments in few rounds compete with
+// short ones that fill the chip.  Measured against fixed heights: FP64
+// 1023 x 770 193 GLUPS at 36 rows (one round of 242 workgroups), 120 at 31 (a
+// second round of 19); 4096^2 303 at 256, 267 at 128.
+template <typename F>
+inline int wave_segment_rows(int ns, int cus, int per_cu, int lo, int ny, F&& groups) {
+    int best = std::max(lo, 1);
+    double t_best = 1e300;
+    for (int segs = 1; segs <= 4096; segs = segs < 32 ? segs + 1 : segs + segs / 16) {
+        const int hs = std::max(lo, (ny + segs - 1) / segs);
+        const double per = std::ceil((double)groups(hs) / cus);
+        const double full = std::floor(per / per_cu), rest = per - full * per_cu;
+        const double t = (hs + 2.0 * ns) * (full * (2.0 + per_cu) + (rest > 0 ? 2.0 + rest : 0.0));
+        if (t < t_best) {
+            t_best = t;
+            best = hs;
+        }
+        if (hs <= lo) break;
+    }
+    return best;
+}
+
+// Steps per launch of the wavefront when the library chooses: twelve for FP64
+// and FP32, eight for half storage, whose launches are bound by instructions
+// and not by HBM (8192^2: 541 GLUPS at eight, 538 at twelve; with stochastic
+// rounding 4096^2 286 and 246).
+inline bool wave_auto(int prec, long long n) { return wave_by_default(prec, n); }
+inline int wave_depth(int prec) { return prec == LBM_FP16 ? 8 : 12; }
+
 // Default steps per launch for `sites` lattice sites (of one lattice, or of
 // all lattices of one storage type in a batch), measured on MI355X: the LDS
 // tile kernel is bound by its per-launch memory phase, so deeper blocking pays
@@ -408,7 +452,7 @@ inline size_t ip_halo_bytes(int prec, int ns, int nx, int ny, int hs = 0) {
 // sites (FP32 1024^2: 232 against 149 GLUPS at four), four on smaller lattices
 // (FP32 256^2: 49 against 42).  FP64 (whose LDS tile is twice as large): five
 // through the tile kernel (1024^2: 106 against 98 GLUPS at four), eight where
-// the register wavefront is the default (wave_by_default, single lattices; a
+// the wavefront is the default (wave_by_default, single lattices; a
 // batch always runs tiles).
 inline int default_time_blocking(int prec, long long sites, bool tiles_only = false) {
     if (prec == LBM_FP64) return (tiles_only || !wave_by_default(prec, sites)) ? 5 : 8;
@@ -552,7 +596,7 @@ struct Lattice {
     int tb = 4;       // plain steps per launch (2..8: fused multi-step kernel)
     int th = 16;      // tile height of the fused LDS kernel (fused_th)
     int th_user = 0;  // tile height chosen by the caller (0: the default)
-    int wave_hs = 0;  // > 0: fused launches use the register wavefront, segments of wave_hs rows
+    int wave_hs = 0;  // > 0: fused launches use the wavefront, segments of wave_hs rows
     int wave_v = 1;   // the wavefront's columns per lane
     int cur = 0;      // buffer with the state at flip 0
     bool inplace = false;  // one buffer, in-place streaming (layout alternates per step)

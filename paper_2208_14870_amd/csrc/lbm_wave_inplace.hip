@@ -12,26 +12,6 @@
 namespace lbm_host {
 
 namespace {
-template <typename S, int V>
-constexpr int kWaveMaxSteps = (V == 2 && std::is_same<S, __half>::value) ? 4 : 8;
-
-template <typename S, int V>
-void launch_wave_ip_t(int ns, unsigned grid, hipStream_t st, const WaveLaunch& W) {
-    switch (ns) {
-        case 2: hipLaunchKernelGGL((k_wave<S, 2, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W); break;
-        case 3: hipLaunchKernelGGL((k_wave<S, 3, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W); break;
-        case 4: hipLaunchKernelGGL((k_wave<S, 4, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W); break;
-        default:
-            if constexpr (kWaveMaxSteps<S, V> == 8) {
-                if (ns == 5) hipLaunchKernelGGL((k_wave<S, 5, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W);
-                else if (ns == 6) hipLaunchKernelGGL((k_wave<S, 6, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W);
-                else if (ns == 7) hipLaunchKernelGGL((k_wave<S, 7, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W);
-                else hipLaunchKernelGGL((k_wave<S, 8, V, false, true>), dim3(grid), dim3(kBlock), 0, st, W);
-            }
-            break;
-    }
-}
-
 template <typename S>
 void launch_halo_t(const WaveLaunch& W, int w, int r, int ns, long long elems, hipStream_t st) {
     const long long want = (elems + kBlock - 1) / kBlock;
@@ -45,7 +25,7 @@ hipError_t launch_wave_inplace(int prec, int ns, int v, int nx, int ny, int hs,
     if (ns < 2 || ns > 8 || hs < 1 || !halo || (v == 2 && (prec == LBM_FP64 || nx % 2 != 0)) ||
         (v == 2 && prec == LBM_FP16 && ns > 4))
         return hipErrorInvalidValue;
-    const int w = wave_width_of(ns, v), r = wave_ring_of(ns, v);
+    const int w = wave_out(ns, v, is_half(prec)), r = wave_ring_of(ns, v);
     WaveLaunch W;
     W.slots = slots;
     W.items = nullptr;
@@ -62,13 +42,15 @@ hipError_t launch_wave_inplace(int prec, int ns, int v, int nx, int ny, int hs,
     else launch_halo_t<__half>(W, w, r, ns, elems, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long long waves = (long long)W.strips * W.segs;
-    const unsigned grid = (unsigned)((waves + kBlock / kWave - 1) / (kBlock / kWave));
-    if (prec == LBM_FP64) launch_wave_ip_t<double, 1>(ns, grid, st, W);
-    else if (prec == LBM_FP32 && v == 2) launch_wave_ip_t<float, 2>(ns, grid, st, W);
-    else if (prec == LBM_FP32) launch_wave_ip_t<float, 1>(ns, grid, st, W);
-    else if (v == 2) launch_wave_ip_t<__half, 2>(ns, grid, st, W);
-    else launch_wave_ip_t<__half, 1>(ns, grid, st, W);
+    const unsigned grid = (unsigned)((long long)W.strips * W.segs);
+    auto run = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, W);
+    };
+    if (prec == LBM_FP64) wave_dispatch<double, 1, false, true, false, false>(ns, run);
+    else if (prec == LBM_FP32 && v == 2) wave_dispatch<float, 2, false, true, false, false>(ns, run);
+    else if (prec == LBM_FP32) wave_dispatch<float, 1, false, true, false, false>(ns, run);
+    else if (v == 2) wave_dispatch<__half, 2, false, true, false, false>(ns, run);
+    else wave_dispatch<__half, 1, false, true, false, false>(ns, run);
     return hipGetLastError();
 }
 
