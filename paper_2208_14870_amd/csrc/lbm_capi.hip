@@ -143,7 +143,14 @@ struct lbm_solver {
         const bool gen = L.general();
         if (L.tb < 2 || (gen ? L.sr_on() || (!fused_auto && L.wave_hs == 0) : !L.fused())) return;
         const bool chosen = !fused_auto || !depth_auto || L.th_user > 0;
-        if (!gen && (chosen ? L.wave_hs == 0 : !wave_auto(prec, L.N) && L.tile_fits())) return;
+        const int sq = chosen ? 0 : square_depth(L.nx, L.ny, cus);
+        if (!gen && (chosen ? L.wave_hs == 0 : !wave_auto(prec, L.N, L.sr_on()) && sq == 0 && L.tile_fits()))
+            return;
+        if (sq > 0) {
+            plan.square = true;
+            plan.ns = sq;
+            return;
+        }
         plan.wave = true;
         plan.ns = depth_auto && fused_auto ? wave_depth(prec) : L.tb;
         plan.v = wave_cols(prec, plan.ns, L.nx, L.ny);
@@ -159,10 +166,13 @@ struct lbm_solver {
     // steps are left: a full launch, else the remainder as one shorter launch
     // where a kernel exists for it (the wavefront: up to eight steps, 9..11 as
     // two launches), else a single step.
-    int depth() const { return plan.wave ? plan.ns : (L.fused() ? L.tb : 1); }
+    int depth() const {
+        return plan.wave || plan.square ? plan.ns : (L.fused() ? L.tb : 1);
+    }
     int next_span(long long rem) const {
         const int d = depth();
         if (rem >= d) return d;
+        if (plan.square) return (int)std::max(1LL, rem);
         if (plan.wave) return rem <= 8 ? (int)std::max(1LL, rem) : (rem == 9 ? 5 : 8);
         return (rem >= 2 && stepN_supported(L.prec, (int)rem, L.th)) ? (int)rem : 1;
     }
@@ -184,7 +194,7 @@ struct lbm_solver {
         hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, stream, d_count, nitems);
         hipLaunchKernelGGL(k_build_items, dim3(blocks_for(nitems)), dim3(kBlock), 0, stream,
                            d_items, 0, 0, d.tiles_x, nitems,
-                           (L.fused() && !plan.wave) ? kItemBand : 0);
+                           (L.fused() && !plan.wave && !plan.square) ? kItemBand : 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "descriptor upload");
         unsigned g = (unsigned)((nitems + 7) / 8 * 8);
@@ -226,6 +236,9 @@ struct lbm_solver {
             plan.wave
                 ? launch_wave(L.prec, ns, plan.v, L.nx, L.ny, plan.hs, d_desc, (int)(ph & 1), st,
                               L.sr_on(), L.general())
+            : plan.square
+                ? launch_stepS(L.prec, ns, L.nx, L.ny, d_desc, (int)(ph & 1), st, L.sr_on(),
+                               L.general())
                 : launch_stepN(L.prec, ns, L.th, grid, st, launch_args((int)(ph & 1)), false,
                                L.sr_on());
         ++ph;  // one buffer flip for ns steps
@@ -300,9 +313,10 @@ struct lbm_solver {
         if (!L.fused() || L.inplace || !L.tile_fits()) return 0;
         const int d = depth();
         const long long r = n % d;
+        const bool own = plan.wave || plan.square;  // plain launches not of the tile kernel
         long long k = r >= 2 ? r : d;
-        if (plan.wave) k = (r >= 2 && r <= 4) ? r : r == 1 ? 5 : r == 5 ? 3 : 4;
-        while (plan.wave && k > 2 && (k > n || !stepN_supported(L.prec, (int)k, L.th))) --k;
+        if (own) k = (r >= 2 && r <= 4) ? r : r == 1 ? 5 : r == 5 ? 3 : 4;
+        while (own && k > 2 && (k > n || !stepN_supported(L.prec, (int)k, L.th))) --k;
         return (k <= n && stepN_supported(L.prec, (int)k, L.th)) ? (int)k : 0;
     }
 
@@ -388,7 +402,8 @@ struct lbm_solver {
         const int flip0 = (int)(phase & 1);
         const int kind = (writeu ? 1 : 0) | (check ? 2 : 0) | (L.general() ? 4 : 0) |
                          (L.inplace ? 8 : 0) | (L.sr_on() ? 16 : 0);
-        const int shape = depth() | (L.th << 4) | (plan.wave ? 1 << 10 | plan.v << 11 : 0);
+        const int shape = depth() | (L.th << 4) | (plan.wave ? 1 << 10 | plan.v << 11 : 0) |
+                          (plan.square ? 1 << 13 : 0);
         auto key = std::make_tuple(nplain, kind, flip0 ^ (L.cur << 1), L.prec, L.eff_vy(), shape,
                                    plan.wave ? plan.hs : 0, grid);
         auto it = graphs.find(key);

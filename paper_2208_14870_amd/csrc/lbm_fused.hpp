@@ -116,10 +116,10 @@ __device__ __forceinline__ S* at_u32(S* base, unsigned i) {
 // step divides or compares coordinates again, and packed into one register per
 // slot (i in bits 0-7, j in bits 8-15, lvl + 1 from bit 16), so that "lvl >= m"
 // is one unsigned compare against a constant.
-template <int TH, int NS, int NT>
+template <int TH, int NS, int NT, int TW = kTW>
 struct SlotGeo {
     static constexpr int R = NS - 1;
-    static constexpr int RW = kTW + 2 * R, RH = TH + 2 * R, RN = RW * RH;
+    static constexpr int RW = TW + 2 * R, RH = TH + 2 * R, RN = RW * RH;
     static constexpr int NM = (RN + NT - 1) / NT;
     static_assert(RW < 256 && RH < 256, "region coordinates must fit 8 bits");
     unsigned p[NM];
@@ -149,15 +149,15 @@ struct SlotGeo {
 // addresses without the periodic wrap; the others wrap every coordinate.
 // stepN_collide1 scales the force, collides and writes the post-collision
 // populations to LDS.
-template <typename S, int TH, int NS, int NT = kBlock, bool SR = false>
+template <typename S, int TH, int NS, int NT = kBlock, bool SR = false, int TW = kTW>
 __device__ __forceinline__ void stepN_load(const S* __restrict__ src,
                                            const typename Store<S>::C* __restrict__ g,
                                            long long plane, int nx, int ny, int x0, int y0,
-                                           const SlotGeo<TH, NS, NT>& geo,
+                                           const SlotGeo<TH, NS, NT, TW>& geo,
                                            typename Store<S>::C f[][8],
                                            typename Store<S>::C gx[], typename Store<S>::C gy[],
                                            unsigned sid[]) {
-    using Geo = SlotGeo<TH, NS, NT>;
+    using Geo = SlotGeo<TH, NS, NT, TW>;
     constexpr int R = Geo::R, NM = Geo::NM;
     using C = typename Store<S>::C;
     const S* pq[8];  // wave-uniform plane bases
@@ -165,7 +165,7 @@ __device__ __forceinline__ void stepN_load(const S* __restrict__ src,
     for (int q = 0; q < 8; ++q) pq[q] = src + q * plane;
     const C* g1 = g + plane;
     const unsigned w = (unsigned)nx;
-    const bool interior = x0 - R >= 1 && x0 + kTW + R <= nx - 1 && y0 - R >= 1 &&
+    const bool interior = x0 - R >= 1 && x0 + TW + R <= nx - 1 && y0 - R >= 1 &&
                           y0 + TH + R <= ny - 1;  // wave-uniform
     if (interior) {
         const unsigned base = (unsigned)(y0 - R) * w + (unsigned)(x0 - R);
@@ -215,10 +215,10 @@ __device__ __forceinline__ void stepN_load(const S* __restrict__ src,
 // collide() forms, taken once per tile.
 // Collides and writes step 1 to LDS; up[a] receives u of the step (for a check
 // launch of two steps, u(n - 1)).
-template <typename S, int TH, int NS, int NT = kBlock>
+template <typename S, int TH, int NS, int NT = kBlock, int TW = kTW, bool GEN = false>
 __device__ __forceinline__ void stepN_collide1(typename Store<S>::C f[][8],
                                                const Coef<typename Store<S>::C>& k, S* lds,
-                                               const SlotGeo<TH, NS, NT>& geo,
+                                               const SlotGeo<TH, NS, NT, TW>& geo,
                                                const typename Store<S>::C gx[],
                                                const typename Store<S>::C gy[],
                                                typename Store<S>::C qg[][2],
@@ -226,14 +226,14 @@ __device__ __forceinline__ void stepN_collide1(typename Store<S>::C f[][8],
                                                const unsigned sid[], bool sr, unsigned sh) {
 #pragma clang fp contract(off)
     using C = typename Store<S>::C;
-    using Geo = SlotGeo<TH, NS, NT>;
+    using Geo = SlotGeo<TH, NS, NT, TW>;
     constexpr int RW = Geo::RW, RN = Geo::RN, NM = Geo::NM;
 #pragma unroll
     for (int a = 0; a < NM; ++a) {
         const int e = (int)threadIdx.x + a * NT;
         qg[a][0] = C(0.25) * (gx[a] * k.gscale);
         qg[a][1] = C(0.25) * (gy[a] * k.gscale);
-        collide_q<C, false>(f[a], qg[a][0], qg[a][1], k, up[a][0], up[a][1]);
+        collide_q<C, GEN>(f[a], qg[a][0], qg[a][1], k, up[a][0], up[a][1]);
         if (geo.active(a, 0)) {
             if constexpr (std::is_same<S, __half>::value) {
                 if (sr) {
@@ -296,17 +296,18 @@ __device__ __forceinline__ void block_reduce3n(double& a, double& b, double& m, 
 // the last (up), and the last step stores u(n) (FP64, unscaled, into u) and
 // reduces sum |u(n) - u(n - 1)|^2, sum |u(n)|^2 and max |f*| over the tile into
 // partial[0..2], as a check step after a write-u step does.
-template <typename S, int TH, int NS, int NT = kBlock, int MODE = kPlain>
+template <typename S, int TH, int NS, int NT = kBlock, int MODE = kPlain, int TW = kTW,
+          bool GEN = false>
 __device__ __forceinline__ void stepN_rest(S* __restrict__ dst, long long plane, int nx, int ny,
                                            int x0, int y0, const Coef<typename Store<S>::C>& k,
-                                           S* lds, const SlotGeo<TH, NS, NT>& geo,
+                                           S* lds, const SlotGeo<TH, NS, NT, TW>& geo,
                                            const typename Store<S>::C qg[][2],
                                            typename Store<S>::C up[][2], double* u,
                                            double inv_scale, double* partial, double* red,
                                            const unsigned sid[], bool sr, unsigned step0,
                                            unsigned seed) {
     using C = typename Store<S>::C;
-    using Geo = SlotGeo<TH, NS, NT>;
+    using Geo = SlotGeo<TH, NS, NT, TW>;
     constexpr int R = Geo::R, RW = Geo::RW, RN = Geo::RN, NM = Geo::NM;
     S* pq[8];  // wave-uniform plane bases
 #pragma unroll
@@ -320,7 +321,7 @@ __device__ __forceinline__ void stepN_rest(S* __restrict__ dst, long long plane,
             if (geo.active(a, m)) {
                 C f[8], ux, uy;
                 lds_read<S, RW, RN>(lds, e, even, f);
-                collide_q<C, false>(f, qg[a][0], qg[a][1], k, ux, uy);
+                collide_q<C, GEN>(f, qg[a][0], qg[a][1], k, ux, uy);
                 bool rounded = false;
                 if constexpr (std::is_same<S, __half>::value) {
                     if (sr) {
@@ -348,7 +349,7 @@ __device__ __forceinline__ void stepN_rest(S* __restrict__ dst, long long plane,
         if (geo.active(a, R) && x < nx && y < ny) {  // the tile, inside the lattice
             C f[8], ux, uy;
             lds_read<S, RW, RN>(lds, e, last_even, f);
-            collide_q<C, false>(f, qg[a][0], qg[a][1], k, ux, uy);
+            collide_q<C, GEN>(f, qg[a][0], qg[a][1], k, ux, uy);
             const unsigned sidx = (unsigned)y * (unsigned)nx + (unsigned)x;
             bool rounded = false;
             if constexpr (std::is_same<S, __half>::value) {
@@ -428,6 +429,61 @@ static __global__ __launch_bounds__(NT) void k_stepN(StepLaunch L) {
                                         x0, y0, k, lds, geo, qg, up, d.u, d.inv_scale,
                                         L.partial + 3 * it, red, sid, sr, d.sr_step, d.sr_seed);
     }
+}
+
+// ---------------------------------------------------------------------------
+// small lattices: a square region of one site per thread
+// ---------------------------------------------------------------------------
+// The same steps over regions of 32 x 32 sites by 1024 threads (tiles of
+// 32 - 2 (NS - 1) a side: 18 at eight steps).  A lattice of up to about 10^5
+// sites does not fill the chip with 64-wide tiles and its launches are bound by
+// latency, not throughput: what counts is the length of one workgroup's chain
+// (descriptor, loads, then per step an LDS read, a collision, an LDS write and a
+// barrier) and the number of launches.  One site per thread makes a step's chain
+// as short as it gets, and the region leaves room for eight steps per launch
+// where the 64-wide tile runs four (FP32) or five (FP64).  The tile follows from
+// the block index (no work list to read).  Of a launch at 288^2 and eight steps
+// (FP64 8.4 us, FP32 6.3 us), 1.9 us are the launch itself, 2.2 (1.6) the loads
+// and the first step, 3.9 (2.4) the other seven steps; figures against the
+// 64-wide tile are with the rule that selects it (square_depth).
+constexpr int kSquare = 32;
+
+struct SquareLaunch {
+    const SlotDesc* slots;
+    int flip;     // launch parity: source buffer = buf[cur ^ flip]
+    int tiles_x;  // tiles per row
+};
+
+template <typename S, int NS, bool SR = false, bool GEN = false>
+static __global__ __launch_bounds__(kSquare* kSquare) void k_stepS(SquareLaunch L) {
+    using C = typename Store<S>::C;
+    constexpr int T = kSquare - 2 * (NS - 1), NT = kSquare * kSquare;
+    using Geo = SlotGeo<T, NS, NT, T>;
+    static_assert(Geo::NM == 1 && Geo::RN == NT, "one site per thread");
+    __shared__ S lds[8 * Geo::RN];
+    const SlotDesc& d = L.slots[0];
+    // each XCD takes a contiguous range of the tiles (shared rows in one L2)
+    const int n = (int)gridDim.x, b = (int)blockIdx.x;
+    const int t = (b % 8) * (n / 8) + min(b % 8, n % 8) + b / 8;
+    const int ty = t / L.tiles_x, tx = t - ty * L.tiles_x;
+    const int x0 = tx * T, y0 = ty * T;
+    Geo geo;
+    geo.init();
+    const int sel = d.cur ^ L.flip;
+    Coef<C> k;
+    k.load(d);
+    C f[1][8], gx[1], gy[1], qg[1][2], up[1][2];
+    constexpr bool sr = SR && std::is_same<S, __half>::value;
+    unsigned sid[1];
+    stepN_load<S, T, NS, NT, sr, T>(reinterpret_cast<const S*>(d.buf[sel]),
+                                    reinterpret_cast<const C*>(d.g), d.plane, d.nx, d.ny, x0, y0,
+                                    geo, f, gx, gy, sid);
+    stepN_collide1<S, T, NS, NT, T, GEN>(f, k, lds, geo, gx, gy, qg, up, sid, sr,
+                                         sr ? sr_step_hash(d.sr_step, d.sr_seed) : 0u);
+    __syncthreads();
+    stepN_rest<S, T, NS, NT, kPlain, T, GEN>(reinterpret_cast<S*>(d.buf[sel ^ 1]), d.plane, d.nx,
+                                             d.ny, x0, y0, k, lds, geo, qg, up, nullptr, 1.0,
+                                             nullptr, nullptr, sid, sr, d.sr_step, d.sr_seed);
 }
 
 }  // namespace lbm

@@ -296,6 +296,37 @@ inline hipError_t launch_stepN(int prec, int ns, int th, unsigned grid, hipStrea
     return hipGetLastError();
 }
 
+// One launch of ns steps (2..12) through the small-lattice kernel: tiles of
+// 32 - 2 (ns - 1) a side from the grid.
+template <typename S, bool SR, bool GEN, int NS = 2>
+inline bool launch_stepS_ns(int ns, unsigned grid, hipStream_t st, const SquareLaunch& L) {
+    if (ns == NS) {
+        hipLaunchKernelGGL((k_stepS<S, NS, SR, GEN>), dim3(grid), dim3(kSquare * kSquare), 0, st, L);
+        return true;
+    }
+    if constexpr (NS < 12) return launch_stepS_ns<S, SR, GEN, NS + 1>(ns, grid, st, L);
+    return false;
+}
+inline hipError_t launch_stepS(int prec, int ns, int nx, int ny, const SlotDesc* slots, int flip,
+                               hipStream_t st, bool sr, bool gen) {
+    if (ns < 2 || ns > 12 || (sr && gen)) return hipErrorInvalidValue;
+    const int t = kSquare - 2 * (ns - 1);
+    SquareLaunch L;
+    L.slots = slots;
+    L.flip = flip;
+    L.tiles_x = (nx + t - 1) / t;
+    const unsigned grid = (unsigned)L.tiles_x * (unsigned)((ny + t - 1) / t);
+    bool ok;
+    if (prec == LBM_FP64) ok = gen ? launch_stepS_ns<double, false, true>(ns, grid, st, L)
+                                   : launch_stepS_ns<double, false, false>(ns, grid, st, L);
+    else if (prec == LBM_FP32) ok = gen ? launch_stepS_ns<float, false, true>(ns, grid, st, L)
+                                        : launch_stepS_ns<float, false, false>(ns, grid, st, L);
+    else if (sr) ok = launch_stepS_ns<__half, true, false>(ns, grid, st, L);
+    else ok = gen ? launch_stepS_ns<__half, false, true>(ns, grid, st, L)
+                  : launch_stepS_ns<__half, false, false>(ns, grid, st, L);
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
 // Whole solves of small lattices in one workgroup (k_solve_small): the largest
 // lattices whose two population buffers fit in LDS.
 constexpr int kSmallMax64 = 1152, kSmallMax32 = 2304;
@@ -408,6 +439,7 @@ inline size_t ip_halo_bytes(int prec, int ns, int nx, int ny, int hs = 0) {
 // of hs rows), or the kernel of the nominal shape (Lattice::tb, th, wave_hs).
 struct PlainPlan {
     bool wave = false;
+    bool square = false;  // the small-lattice kernel
     int ns = 0, v = 1, hs = 0;
 };
 
@@ -442,7 +474,37 @@ inline int wave_segment_rows(int ns, int cus, int per_cu, int lo, int ny, F&& gr
 // and FP32, eight for half storage, whose launches are bound by instructions
 // and not by HBM (8192^2: 541 GLUPS at eight, 538 at twelve; with stochastic
 // rounding 4096^2 286 and 246).
-inline bool wave_auto(int prec, long long n) { return wave_by_default(prec, n); }
+// Lattices whose plain steps run through the wavefront when the library chooses
+// (us per step, 64-wide tile / wavefront): FP64 from 150000 sites (400^2
+// 2.49 / 2.08, 320 x 300 1.66 / 1.90; where k_stepS applies it is faster than
+// both), FP32 from 327680 (600^2 2.40 / 2.18, 500 x 512 1.68 / 1.96), FP16 from
+// 2^20 (1200^2 4.93 / 4.53, 850^2 2.97 / 3.13), with stochastic rounding from
+// 2^21 (1700^2 15.1 / 12.6, 1200^2 8.1 / 8.3).
+inline bool wave_auto(int prec, long long n, bool sr) {
+    if (prec == LBM_FP64) return n >= 150000;
+    if (prec == LBM_FP32) return n >= 327680;
+    return n >= (sr ? 1LL << 21 : 1LL << 20);
+}
+// Tiles of the small-lattice kernel (k_stepS) at ns steps per launch, and the
+// depth it runs at: the deepest of 4..12 whose tiles are no more than the
+// compute units, 0 when there is none.  Its launches are chains of latencies
+// (FP64 about 5.5 us and 0.4 us per step, FP32 4.3 and 0.3), so a second
+// workgroup on a compute unit costs more than a shallower launch.  Measured, us
+// per step, 64-wide tile or wavefront / this kernel: FP64 64^2 1.52 / 0.86,
+// 240 x 200 1.62 / 1.06 (nine steps; ten, on 300 tiles, 1.33), 400^2
+// 2.07 / 1.89 (four steps), 440^2 2.2 / 2.5 (three); FP32 64^2 1.22 / 0.66,
+// 240 x 200 1.38 / 0.79, 400^2 1.62 / 1.32; FP16 240 x 200 1.84 / 0.79; free
+// rates FP64 288^2 2.28 / 1.14.
+inline int square_tile(int ns) { return kSquare - 2 * (ns - 1); }
+inline long long square_tiles(int ns, int nx, int ny) {
+    const int t = square_tile(ns);
+    return (long long)((nx + t - 1) / t) * ((ny + t - 1) / t);
+}
+inline int square_depth(int nx, int ny, int cus) {
+    for (int ns = 12; ns >= 4; --ns)
+        if (square_tiles(ns, nx, ny) <= cus) return ns;
+    return 0;
+}
 inline int wave_depth(int prec) { return prec == LBM_FP16 ? 8 : 12; }
 
 // Default steps per launch for `sites` lattice sites (of one lattice, or of

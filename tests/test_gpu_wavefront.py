@@ -80,3 +80,21 @@ def test_default_depth_stochastic_rounding():
     """Half storage with stochastic rounding at the default's eight steps."""
     say("default depth fp16 sr 4097x4096")
     _pair(4097, 4096, "fp16", steps=(8, 3), sr=True)
+
+
+# one tile, one and two beyond a tile of 10 (twelve steps), 18 (eight) and 26
+# (four) a side, more rows or columns than the other way round, and the largest
+# square lattice of the small-lattice rule
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("nx,ny", [(1, 3), (10, 10), (11, 31), (33, 9), (160, 161), (289, 288),
+                                   (18, 3000), (2700, 20), (416, 416), (417, 416)])
+def test_small_lattices_equal_single_steps(prec, nx, ny):
+    """Default launches of small lattices at every depth the rule picks (deeper
+    for fewer tiles), with every remainder."""
+    say(f"small lattice {prec} {nx}x{ny}")
+    _pair(nx, ny, prec, steps=(12, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2, 1, 29))
+
+
+def test_small_lattice_stochastic_rounding():
+    say("small lattice fp16 sr 200x190")
+    _pair(200, 190, "fp16", steps=(9, 13, 2), sr=True)
