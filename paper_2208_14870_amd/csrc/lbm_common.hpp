@@ -380,6 +380,49 @@ __device__ __forceinline__ double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
     return v;
 }
+// The same sums (the same pairs, in either order) through lane swaps and row
+// rotations, without LDS: the partner of a lane at distance 32 and 16 by swapping
+// half rows, at 8, 4, 2, 1 by rotating a row of 16, whose values repeat with that
+// period by then.
+template <int CTRL>
+__device__ __forceinline__ double row_rotated(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// sum over a row of 16 lanes
+__device__ __forceinline__ double row_sum(double v) {
+    v += row_rotated<0x128>(v);  // row_ror:8
+    v += row_rotated<0x124>(v);
+    v += row_rotated<0x122>(v);
+    v += row_rotated<0x121>(v);
+    return v;
+}
+// halves of 32 (16) lanes swapped: a keeps its lower half and gets b's lower
+// half above it, b gets a's upper half below its own
+__device__ __forceinline__ void swap_halves32(double& a, double& b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+    b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void swap_halves16(double& a, double& b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+    b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+// Two sums at once: lanes 0..31 return the sum of a, lanes 32..63 that of b.
+__device__ __forceinline__ double wave_sum2(double a, double b) {
+    swap_halves32(a, b);
+    double v = a + b, w;
+    w = v;
+    swap_halves16(v, w);
+    return row_sum(v + w);
+}
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
@@ -485,6 +528,45 @@ struct RiseGuard {
         if (count < kWindow) ++count;
         prev = d;
         return M > 0 && run >= M && d >= 2.0 * base;
+    }
+};
+
+// The same guard fed with d^2, for the one-workgroup solve: the square root is
+// monotone, so a d^2 that did not rise needs none, and the largest of several
+// square roots is that of the largest.  prev, base and hist hold squares here;
+// one wave keeps it, the ring in LDS.
+struct RiseGuardSq {
+    double prev, base;
+    int run, count, pos;
+    __device__ void load(const RiseGuard& g) {
+        prev = g.prev;
+        base = g.base;
+        run = g.run;
+        count = g.count;
+        pos = g.pos;
+    }
+    __device__ void store(RiseGuard& g) const {
+        g.prev = prev;
+        g.base = base;
+        g.run = run;
+        g.count = count;
+        g.pos = pos;
+    }
+    __device__ bool update(double d2, int M, double* hist) {
+        if (d2 > prev && sqrt(d2) > sqrt(prev)) {
+            if (run == 0) {
+                base = hist[0];
+                for (int h = 1; h < count; ++h) base = fmax(base, hist[h]);
+            }
+            ++run;
+        } else {
+            run = 0;
+        }
+        hist[pos] = d2;
+        pos = (pos + 1) % RiseGuard::kWindow;
+        if (count < RiseGuard::kWindow) ++count;
+        prev = d2;
+        return M > 0 && run >= M && sqrt(d2) >= 2.0 * sqrt(base);
     }
 };
 
