@@ -1245,14 +1245,9 @@ int lbm_error_norms(lbm_solver* s, const double* ux_ref, const double* uy_ref, d
     if (!s) return LBM_E_ARG;
     if (!ux_ref || !uy_ref || !out) return s->fail(LBM_E_ARG, "error_norms: NULL argument");
     if (!s->L.has_force) return s->fail(LBM_E_STATE, "error_norms: no body force set");
-    // displacement into the u planes of the workspace, then the two-stage reduction
-    double* ux = s->L.mem.u;
-    double* uy = s->L.mem.u + s->L.plane;
-    hipError_t e = extract_u(s->L.prec, s->L.desc(), s->sel(), s->L.layout(s->sel()), ux, uy,
-                             s->stream);
+    hipError_t e = launch_err_norms(s->L.prec, s->L.desc(), s->sel(), s->L.layout(s->sel()), ux_ref,
+                                    uy_ref, s->d_red, s->stream);
     if (e != hipSuccess) return s->hip_fail(e, "error_norms");
-    hipLaunchKernelGGL(k_err_norms, dim3(kErrBlocks), dim3(kBlock), 0, s->stream, ux, uy, ux_ref,
-                       uy_ref, s->L.N, s->d_red);
     hipLaunchKernelGGL(k_reduce4<kErrMask>, dim3(1), dim3(kBlock), 0, s->stream, s->d_red,
                        kErrBlocks, s->d_red + 4 * kErrBlocks);
     if ((e = hipGetLastError()) == hipSuccess)
@@ -1338,11 +1333,14 @@ int lbm_set_populations(lbm_solver* s, const double* f) {
     const SlotDesc d = s->L.desc();
     const double sc = d.gscale;
     hipError_t e;
-    if (s->L.prec == LBM_FP64) e = launch_set_f<double>(d, s->sel(), s->L.layout(s->sel()), f, sc, s->stream);
-    else if (s->L.prec == LBM_FP32) e = launch_set_f<float>(d, s->sel(), s->L.layout(s->sel()), f, sc, s->stream);
-    else e = launch_set_f<__half>(d, s->sel(), s->L.layout(s->sel()), f, sc, s->stream);
-    if (e == hipSuccess && !s->L.inplace)  // in place: no polish switch, no targets
-        e = neutral_measure(s->L.prec, d, s->sel(), s->d_red, s->h_result, s->stream);
+    if (!s->L.inplace) {
+        e = set_f_measured(s->L.prec, d, s->sel(), f, sc, s->d_red, s->h_result, s->stream);
+    } else {  // no polish switch, no targets
+        const int lay = s->L.layout(s->sel());
+        if (s->L.prec == LBM_FP64) e = launch_set_f<double>(d, s->sel(), lay, f, sc, s->stream);
+        else if (s->L.prec == LBM_FP32) e = launch_set_f<float>(d, s->sel(), lay, f, sc, s->stream);
+        else e = launch_set_f<__half>(d, s->sel(), lay, f, sc, s->stream);
+    }
     if (e != hipSuccess) return s->hip_fail(e, "set_populations");
     if (!s->L.inplace) {
         // the given state starts the exact trajectory: its mean first moments,

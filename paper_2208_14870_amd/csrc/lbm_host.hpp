@@ -748,6 +748,20 @@ inline hipError_t extract_u(int prec, const SlotDesc& d, int sel, int layout, do
     return launch_extract_u<__half>(d, sel, layout, ux, uy, st);
 }
 
+// Block partials of the error norms of a state (kErrBlocks x 4).
+inline hipError_t launch_err_norms(int prec, const SlotDesc& d, int sel, int layout,
+                                   const double* rx, const double* ry, double* partial,
+                                   hipStream_t st) {
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(kErrBlocks), dim3(kBlock), 0, st, d, sel, layout, rx, ry,
+                           partial);
+    };
+    if (prec == LBM_FP64) run(k_err_norms_state<double>);
+    else if (prec == LBM_FP32) run(k_err_norms_state<float>);
+    else run(k_err_norms_state<__half>);
+    return hipGetLastError();
+}
+
 template <typename S>
 inline hipError_t launch_stress(const SlotDesc& d, int sel, int layout, const Rates& r, double* a,
                                 double* b, double* c, hipStream_t st) {
@@ -792,29 +806,25 @@ inline hipError_t zero_bytes(void* p, size_t bytes, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Measure the neutral modes of the stored state (blocking): out[0..3] =
-// staggered sums and their force terms, out[4..5] = sum m10, sum m01.
-// scratch: 8 * kErrBlocks + 12 doubles of device memory; host: 8 pinned doubles.
-template <typename S>
-inline hipError_t neutral_measure_t(const SlotDesc& d, int sel, double* scratch, double* host,
-                                    hipStream_t st) {
-    hipLaunchKernelGGL(k_neutral_sums<S>, dim3(kErrBlocks), dim3(kBlock), 0, st, d, sel, scratch);
+// Store a state f(n) given in the paper's order into a buffer in kLayPull and
+// measure its neutral modes (blocking): out[0..3] = staggered sums and their
+// force terms, out[4..5] = sum m10, sum m01.  scratch: 8 * kErrBlocks + 12
+// doubles of device memory; host: 8 pinned doubles.
+inline hipError_t set_f_measured(int prec, const SlotDesc& d, int sel, const double* f, double scale,
+                                 double* scratch, double* host, hipStream_t st) {
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(kErrBlocks), dim3(kBlock), 0, st, d, sel, f, scale, scratch);
+    };
+    if (prec == LBM_FP64) run(k_set_f_sums<double>);
+    else if (prec == LBM_FP32) run(k_set_f_sums<float>);
+    else run(k_set_f_sums<__half>);
     double* out = scratch + 8 * kErrBlocks;
-    hipLaunchKernelGGL(k_reduce4<0>, dim3(1), dim3(kBlock), 0, st, scratch, kErrBlocks, out);
-    hipLaunchKernelGGL(k_reduce4<0>, dim3(1), dim3(kBlock), 0, st, scratch + 4 * kErrBlocks,
-                       kErrBlocks, out + 4);
+    hipLaunchKernelGGL(k_reduce8<0>, dim3(2), dim3(kBlock), 0, st, scratch, kErrBlocks, out);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess)
         e = hipMemcpyAsync(host, out, 8 * sizeof(double), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     return e;
-}
-
-inline hipError_t neutral_measure(int prec, const SlotDesc& d, int sel, double* scratch,
-                                  double* host, hipStream_t st) {
-    if (prec == LBM_FP64) return neutral_measure_t<double>(d, sel, scratch, host, st);
-    if (prec == LBM_FP32) return neutral_measure_t<float>(d, sel, scratch, host, st);
-    return neutral_measure_t<__half>(d, sel, scratch, host, st);
 }
 
 // Reset the neutral modes of the stored state to their exact values: the
@@ -828,9 +838,7 @@ inline hipError_t neutral_reset_t(const SlotDesc& d, int sel, const double mean_
                                   const double stag_target[2], double* scratch, hipStream_t st) {
     hipLaunchKernelGGL(k_neutral_sums<S>, dim3(kErrBlocks), dim3(kBlock), 0, st, d, sel, scratch);
     double* out = scratch + 8 * kErrBlocks;
-    hipLaunchKernelGGL(k_reduce4<0>, dim3(1), dim3(kBlock), 0, st, scratch, kErrBlocks, out);
-    hipLaunchKernelGGL(k_reduce4<0>, dim3(1), dim3(kBlock), 0, st, scratch + 4 * kErrBlocks,
-                       kErrBlocks, out + 4);
+    hipLaunchKernelGGL(k_reduce8<0>, dim3(2), dim3(kBlock), 0, st, scratch, kErrBlocks, out);
     double* coef = out + 8;
     hipLaunchKernelGGL(k_neutral_coef, dim3(1), dim3(1), 0, st, out, (double)d.nx * d.ny,
                        d.nx % 2 == 0 ? 1 : 0, d.ny % 2 == 0 ? 1 : 0, mean_target[0],
@@ -854,10 +862,8 @@ inline hipError_t neutral_reset(int prec, const SlotDesc& d, int sel, const doub
 // memory.  Stream-ordered.
 inline hipError_t force_stats(const ForceSrc& src, double* scratch, double* stats, hipStream_t st) {
     hipLaunchKernelGGL(k_force_stats8, dim3(kErrBlocks), dim3(kBlock), 0, st, src, scratch);
-    hipLaunchKernelGGL(k_reduce4<kForceMask>, dim3(1), dim3(kBlock), 0, st, scratch, kErrBlocks,
+    hipLaunchKernelGGL(k_reduce8<kForceMask>, dim3(2), dim3(kBlock), 0, st, scratch, kErrBlocks,
                        stats);
-    hipLaunchKernelGGL(k_reduce4<0>, dim3(1), dim3(kBlock), 0, st, scratch + 4 * kErrBlocks,
-                       kErrBlocks, stats + 4);
     return hipGetLastError();
 }
 

@@ -2,6 +2,8 @@
 // conversions, FP64 norms, the work list and the neutral-mode reset.
 #pragma once
 
+#include <type_traits>
+
 #include "lbm_common.hpp"
 
 namespace lbm {
@@ -10,8 +12,18 @@ namespace lbm {
 // per-lattice helpers (1 thread per site)
 // ---------------------------------------------------------------------------
 
-// u(n) = bared first moments of f(n) (read from the stored field in its
-// layout), FP64 and unscaled (Table "solution").
+// Displacement of a site from its populations f(n) and force, FP64 and unscaled
+// (bared first moments, Table "solution").
+template <typename C>
+__device__ __forceinline__ void displacement_of(const C f[8], double gx, double gy, double gscale,
+                                                double inv_scale, double& ux, double& uy) {
+    const double m10 = (double)((f[0] - f[2]) + ((f[4] - f[6]) - (f[5] - f[7])));
+    const double m01 = (double)((f[1] - f[3]) + ((f[4] - f[6]) + (f[5] - f[7])));
+    ux = (m10 + 0.5 * gx * gscale) * inv_scale;
+    uy = (m01 + 0.5 * gy * gscale) * inv_scale;
+}
+
+// u(n) from the stored field in its layout.
 template <typename S>
 static __global__ __launch_bounds__(kBlock) void k_extract_u(SlotDesc d, int sel, int layout,
                                                              double* ux, double* uy) {
@@ -22,11 +34,10 @@ static __global__ __launch_bounds__(kBlock) void k_extract_u(SlotDesc d, int sel
     C f[8];
     load_state<S>(reinterpret_cast<const S*>(d.buf[sel]), d.plane, d.nx, d.ny, x, y, layout, f);
     const C* g = reinterpret_cast<const C*>(d.g);
-    const double m10 = (double)((f[0] - f[2]) + ((f[4] - f[6]) - (f[5] - f[7])));
-    const double m01 = (double)((f[1] - f[3]) + ((f[4] - f[6]) + (f[5] - f[7])));
-    const double gsc = d.gscale;
-    ux[s] = (m10 + 0.5 * (double)g[s] * gsc) * d.inv_scale;
-    uy[s] = (m01 + 0.5 * (double)g[d.plane + s] * gsc) * d.inv_scale;
+    double vx, vy;
+    displacement_of<C>(f, (double)g[s], (double)g[d.plane + s], d.gscale, d.inv_scale, vx, vy);
+    ux[s] = vx;
+    uy[s] = vy;
 }
 
 // Stress from the bared second-order moments of f(n) (Eq. compute_bared with
@@ -159,6 +170,38 @@ static __global__ __launch_bounds__(kBlock) void k_err_norms(const double* ux, c
         v[1] += rx[i] * rx[i] + ry[i] * ry[i];
         v[2] = fmax(v[2], fmax(fabs(ex), fabs(ey)));
         v[3] = fmax(v[3], fmax(fabs(rx[i]), fabs(ry[i])));
+    }
+    block_reduce4<kErrMask>(v, lds);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 4; ++c) partial[4 * blockIdx.x + c] = v[c];
+}
+
+// The same norms of the displacement of a stored state, formed as k_extract_u
+// forms it, without a pass through memory: reading the state and the reference
+// once, instead of writing u and reading it back (2048 x 1500 FP32 49 us for the
+// two kernels).  Block partials and their order are those of k_err_norms.
+template <typename S>
+static __global__ __launch_bounds__(kBlock) void k_err_norms_state(SlotDesc d, int sel, int layout,
+                                                                   const double* rx,
+                                                                   const double* ry,
+                                                                   double* partial) {
+    using C = typename Store<S>::C;
+    __shared__ double lds[16];
+    const unsigned n = (unsigned)((long long)d.nx * d.ny), step = gridDim.x * kBlock;
+    const S* st = reinterpret_cast<const S*>(d.buf[sel]);
+    const C* g = reinterpret_cast<const C*>(d.g);
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (unsigned s = blockIdx.x * kBlock + threadIdx.x; s < n; s += step) {
+        const int y = (int)(s / (unsigned)d.nx), x = (int)(s - (unsigned)y * (unsigned)d.nx);
+        C f[8];
+        load_state<S>(st, d.plane, d.nx, d.ny, x, y, layout, f);
+        double ux, uy;
+        displacement_of<C>(f, (double)g[s], (double)g[d.plane + s], d.gscale, d.inv_scale, ux, uy);
+        const double ex = ux - rx[s], ey = uy - ry[s];
+        v[0] += ex * ex + ey * ey;
+        v[1] += rx[s] * rx[s] + ry[s] * ry[s];
+        v[2] = fmax(v[2], fmax(fabs(ex), fabs(ey)));
+        v[3] = fmax(v[3], fmax(fabs(rx[s]), fabs(ry[s])));
     }
     block_reduce4<kErrMask>(v, lds);
     if (threadIdx.x == 0)
@@ -303,6 +346,24 @@ static __global__ __launch_bounds__(kBlock) void k_reduce4(const double* partial
         for (int c = 0; c < 4; ++c) out[c] = v[c];
 }
 
+// Stage 2 of two groups of partials (the second nparts entries on), a block
+// each: out[0..3] and out[4..7].
+template <int MAXMASK0>
+static __global__ __launch_bounds__(kBlock) void k_reduce8(const double* partial, int nparts,
+                                                    double* out) {
+    __shared__ double lds[16];
+    const double* p = partial + 4LL * blockIdx.x * nparts;
+    const int mask = blockIdx.x == 0 ? MAXMASK0 : 0;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < nparts; i += kBlock)
+        for (int c = 0; c < 4; ++c)
+            v[c] = ((mask >> c) & 1) ? fmax(v[c], p[4 * i + c]) : v[c] + p[4 * i + c];
+    if (blockIdx.x == 0) block_reduce4<MAXMASK0>(v, lds);
+    else block_reduce4<0>(v, lds);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 4; ++c) out[4 * blockIdx.x + c] = v[c];
+}
+
 // Write the work list of one lattice: tiles in vertical bands `band` tiles
 // wide, each band row by row (band >= tiles_x: row-major order).  Each XCD
 // walks a contiguous slice of the list, so a tile's neighbours above and
@@ -352,6 +413,18 @@ static __global__ void k_add_sr_step(SlotDesc* p, int ns) { p->sr_step += (unsig
 // Stage 1: per block two groups of four sums, unscaled FP64:
 // (sum (-1)^x m10(S), sum (-1)^y m01(S), sum (-1)^x gx, sum (-1)^y gy) and
 // (sum m10(S), sum m01(S), 0, 0).
+__device__ __forceinline__ void neutral_add(const double f[8], double inv_scale, double px,
+                                            double py, double gx, double gy, double v[4],
+                                            double w[4]) {
+    const double m10 = ((f[0] - f[2]) + ((f[4] - f[6]) - (f[5] - f[7]))) * inv_scale;
+    const double m01 = ((f[1] - f[3]) + ((f[4] - f[6]) + (f[5] - f[7]))) * inv_scale;
+    v[0] += px * m10;
+    v[1] += py * m01;
+    v[2] += px * gx;
+    v[3] += py * gy;
+    w[0] += m10;
+    w[1] += m01;
+}
 template <typename S>
 static __global__ __launch_bounds__(kBlock) void k_neutral_sums(SlotDesc d, int sel,
                                                                 double* partial) {
@@ -367,15 +440,52 @@ static __global__ __launch_bounds__(kBlock) void k_neutral_sums(SlotDesc d, int 
         const int x = (int)(s % d.nx), y = (int)(s / d.nx);
         double f[8];
         for (int q = 0; q < 8; ++q) f[q] = (double)Store<S>::ld(st + q * d.plane + s);
-        const double m10 = ((f[0] - f[2]) + ((f[4] - f[6]) - (f[5] - f[7]))) * d.inv_scale;
-        const double m01 = ((f[1] - f[3]) + ((f[4] - f[6]) + (f[5] - f[7]))) * d.inv_scale;
-        const double px = (x & 1) ? -sx : sx, py = (y & 1) ? -sy : sy;
-        v[0] += px * m10;
-        v[1] += py * m01;
-        v[2] += px * (double)g[s];
-        v[3] += py * (double)g[d.plane + s];
-        w[0] += m10;
-        w[1] += m01;
+        neutral_add(f, d.inv_scale, (x & 1) ? -sx : sx, (y & 1) ? -sy : sy, (double)g[s],
+                    (double)g[d.plane + s], v, w);
+    }
+    block_reduce4<0>(v, lds);
+    block_reduce4<0>(w, lds);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 4; ++c) {
+            partial[4 * blockIdx.x + c] = v[c];
+            partial[4 * (gridDim.x + blockIdx.x) + c] = w[c];
+        }
+}
+
+// k_set_f into a buffer in kLayPull and k_neutral_sums of what it stores, in one
+// pass (the same sums in the same order; 2048 x 1500 FP32: the second pass over
+// the stored field took 28 us of 78).
+template <typename S>
+static __global__ __launch_bounds__(kBlock) void k_set_f_sums(SlotDesc d, int sel, const double* in,
+                                                              double scale, double* partial) {
+    __shared__ double lds[16];
+    using C = typename Store<S>::C;
+    const unsigned nx = (unsigned)d.nx, ny = (unsigned)d.ny, n = nx * ny, step = gridDim.x * kBlock;
+    S* dst = reinterpret_cast<S*>(d.buf[sel]);
+    const C* g = reinterpret_cast<const C*>(d.g);
+    const double sx = (nx % 2 == 0) ? 1.0 : 0.0, sy = (ny % 2 == 0) ? 1.0 : 0.0;
+    double v[4] = {0.0, 0.0, 0.0, 0.0}, w[4] = {0.0, 0.0, 0.0, 0.0};
+    for (unsigned s = blockIdx.x * kBlock + threadIdx.x; s < n; s += step) {
+        const unsigned y = s / nx, x = s - y * nx;
+        const unsigned xm = (x == 0 ? nx : x) - 1, xp = x + 1 == nx ? 0 : x + 1;
+        const unsigned r0 = y * nx, rm = (y == 0 ? ny - 1 : y - 1) * nx,
+                       rp = (y + 1 == ny ? 0 : y + 1) * nx;
+        // f*(n-1)_q(x) = f(n)_q(x + c_q)
+        const unsigned at[8] = {r0 + xp, rp + x, r0 + xm, rm + x, rp + xp, rp + xm, rm + xm, rm + xp};
+        double f[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) f[q] = in[(long long)q * n + at[q]] * scale;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            S* p = dst + q * d.plane + s;
+            const C c = (C)f[q];
+            Store<S>::st(p, c);
+            // as the storage type holds it
+            if constexpr (std::is_same<S, __half>::value) f[q] = (double)__half2float(__float2half_rn(c));
+            else f[q] = (double)c;
+        }
+        neutral_add(f, d.inv_scale, (x & 1) ? -sx : sx, (y & 1) ? -sy : sy, (double)g[s],
+                    (double)g[d.plane + s], v, w);
     }
     block_reduce4<0>(v, lds);
     block_reduce4<0>(w, lds);
