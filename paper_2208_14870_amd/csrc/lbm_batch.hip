@@ -321,14 +321,21 @@ struct lbm_batch {
             const int hs = wave_ny ? wave_segment_rows(tb[p], cus, wave_blocks_per_cu(p, tb[p], 1),
                                                        16, wave_ny, groups)
                                    : 1;
+            // segments of equal height per lattice, the longest first: the last
+            // round of workgroups then ends with short ones
             for (int i = 0; i < max_slots && w > 0; ++i) {
                 const BSlot& s = slots[i];
                 if (!s.active || s.L.prec != p || !s.wave) continue;
-                const int strips = (s.L.nx + w - 1) / w;
-                for (int ya = 0; ya < s.L.ny; ya += hs)
+                const int strips = (s.L.nx + w - 1) / w, segs = (s.L.ny + hs - 1) / hs;
+                const int rows = (s.L.ny + segs - 1) / segs;
+                for (int ya = 0; ya < s.L.ny; ya += rows)
                     for (int sx = 0; sx < strips; ++sx)
-                        h_witems.push_back(WaveItem{i, sx, ya, std::min(ya + hs, s.L.ny)});
+                        h_witems.push_back(WaveItem{i, sx, ya, std::min(ya + rows, s.L.ny)});
             }
+            std::stable_sort(h_witems.begin() + wrange_host[p][0], h_witems.end(),
+                             [](const WaveItem& a, const WaveItem& b) {
+                                 return a.yb - a.ya > b.yb - b.ya;
+                             });
             wrange_host[p][1] = (int)h_witems.size();
         }
         if (total > cap_items || (long long)h_witems.size() > cap_items)
