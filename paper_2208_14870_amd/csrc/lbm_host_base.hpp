@@ -46,13 +46,19 @@ inline bool is_half(int prec) { return prec == LBM_FP16; }
 // launch of ns steps reads (k_wave_halo), in bytes: per strip boundary 2R
 // columns of every row, per segment boundary 2 ns rows of every column, eight
 // planes each.  The column copies come first, the row copies at
-// wave_halo_x_bytes.  wave_halo_bytes is the room a caller provides: it counts
-// strips of one wave (64 v columns less the ring), of which there are at least
-// as many as the launch's own strips (a wave or two side by side).
+// wave_halo_x_bytes (wave_halo_used together).  wave_halo_bytes is the room a
+// caller provides: it counts strips of one wave (64 v columns less the ring), of
+// which there are at least as many as the launch's own strips (a wave or two
+// side by side).
 inline size_t wave_halo_x_bytes(int prec, int ns, int v, int nx, int ny) {
     const int w = wave_out(ns, v, is_half(prec)), r = wave_ring_of(ns, v);
     const long long strips = (nx + w - 1) / w;
     return al((size_t)(8 * strips * 2LL * r * ny) * elem_bytes(prec));
+}
+inline size_t wave_halo_used(int prec, int ns, int v, int nx, int ny, int hs) {
+    const long long segs = (ny + hs - 1) / hs;
+    return wave_halo_x_bytes(prec, ns, v, nx, ny) +
+           al((size_t)(8 * segs * 2LL * ns * nx) * elem_bytes(prec));
 }
 inline size_t wave_halo_bytes(int prec, int ns, int v, int nx, int ny, int hs) {
     const int r = wave_ring_of(ns, v), w = kWave * v - 2 * r;

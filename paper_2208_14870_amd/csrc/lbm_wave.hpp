@@ -546,7 +546,7 @@ void wave_dispatch(int ns, F&& run) {
     constexpr int kMax = kHalf ? (V == 2 ? 4 : 8) : 12;
     if (ns == NS) run(k_wave<S, NS, V, SR, IP, LIST, GEN>, WaveShape<S, NS, V>::NT);
     else if constexpr (NS < kMax && NS != 8) wave_dispatch<S, V, SR, IP, LIST, GEN, NS + 1>(ns, run);
-    else if constexpr (NS < kMax && !IP) wave_dispatch<S, V, SR, IP, LIST, GEN, 12>(ns, run);
+    else if constexpr (NS < kMax) wave_dispatch<S, V, SR, IP, LIST, GEN, 12>(ns, run);
 }
 
 }  // namespace lbm
