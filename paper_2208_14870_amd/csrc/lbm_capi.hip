@@ -77,7 +77,7 @@ struct lbm_solver {
     int* d_first = nullptr;
     int* d_count = nullptr;
     double* d_partial = nullptr;
-    double* d_result = nullptr;
+    double* d_result = nullptr;  // h_result as the GPU addresses it
     RiseGuard* d_guard = nullptr;  // divergence guard of the one-workgroup solve
     double* d_red = nullptr;  // kErrBlocks x 8 + 16
     double* h_result = nullptr;  // pinned, 8 doubles
@@ -251,8 +251,8 @@ struct lbm_solver {
                 ? launch_wave(L.prec, ns, plan.v, L.nx, L.ny, plan.hs, d_desc, (int)(ph & 1), st,
                               L.sr_on(), L.general())
             : plan.square
-                ? launch_stepS(L.prec, ns, L.nx, L.ny, d_desc, (int)(ph & 1), st, L.sr_on(),
-                               L.general())
+                ? launch_square(L.prec, ns, L.nx, L.ny, d_desc, (int)(ph & 1), d_partial, false, st,
+                                L.sr_on(), L.general())
                 : launch_stepN(L.prec, ns, L.th, grid, st, launch_args((int)(ph & 1)), false,
                                L.sr_on());
         ++ph;  // one buffer flip for ns steps
@@ -289,8 +289,10 @@ struct lbm_solver {
         return e;
     }
 
-    hipError_t enqueue_finalize(hipStream_t st) {
+    // items >= 0: the partials of a launch off the work list
+    hipError_t enqueue_finalize(hipStream_t st, int items = -1) {
         FinalizeLaunch F;
+        F.items = items;
         F.first = d_first;
         F.count = d_count;
         F.partial = d_partial;
@@ -324,13 +326,18 @@ struct lbm_solver {
     // 1023 x 770: 61 us for the two, 105 for a tile launch of eight that carries
     // them, 45 for one of four).
     int check_span(long long n) const {
+        if (plan.square) {  // its own check launch, the remainder of n, at least 2
+            const int d = plan.ns;
+            const long long r = n % d;
+            const long long k = r >= 2 ? r : r == 0 ? d : d < 12 ? d + 1 : 5;
+            return square_tiles((int)k, L.nx, L.ny) <= max_items_ ? (int)k : 0;
+        }
         if (!L.fused() || L.inplace || !L.tile_fits()) return 0;
         const int d = depth();
         const long long r = n % d;
-        const bool own = plan.wave || plan.square;  // plain launches not of the tile kernel
         long long k = r >= 2 ? r : d;
-        if (own) k = (r >= 2 && r <= 4) ? r : r == 1 ? 5 : r == 5 ? 3 : 4;
-        while (own && k > 2 && (k > n || !stepN_supported(L.prec, (int)k, L.th))) --k;
+        if (plan.wave) k = (r >= 2 && r <= 4) ? r : r == 1 ? 5 : r == 5 ? 3 : 4;
+        while (plan.wave && k > 2 && (k > n || !stepN_supported(L.prec, (int)k, L.th))) --k;
         return (k <= n && stepN_supported(L.prec, (int)k, L.th)) ? (int)k : 0;
     }
 
@@ -354,11 +361,14 @@ struct lbm_solver {
             }
         }
         if (e == hipSuccess && span) {
-            e = launch_stepN(L.prec, span, L.th, grid, st, launch_args((int)(ph & 1)), true,
-                             L.sr_on());
+            e = plan.square ? launch_square(L.prec, span, L.nx, L.ny, d_desc, (int)(ph & 1), d_partial,
+                                            true, st, L.sr_on(), L.general())
+                            : launch_stepN(L.prec, span, L.th, grid, st, launch_args((int)(ph & 1)),
+                                           true, L.sr_on());
             ++ph;
             if (e == hipSuccess) e = advance_sr(span, st);
-            if (e == hipSuccess) e = enqueue_finalize(st);
+            if (e == hipSuccess)
+                e = enqueue_finalize(st, plan.square ? (int)square_tiles(span, L.nx, L.ny) : -1);
             return e;
         }
         if (e == hipSuccess && writeu) e = enqueue_one(kWriteU, st, ph);
@@ -504,6 +514,10 @@ static int create_solver(int nx, int ny, int precision, int with_polish, bool in
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->cap, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&s->h_result), 8 * sizeof(double),
                                            hipHostMallocDefault);
+    // results that only the host reads are written by the kernels to this memory
+    // (a copy behind a check is 2.6 us of the device and a dispatch more)
+    if (e == hipSuccess)
+        e = hipHostGetDevicePointer(reinterpret_cast<void**>(&s->d_result), s->h_result, 0);
     if (e != hipSuccess) {
         g_create_error = std::string("lbm_create: ") + hipGetErrorString(e);
         if (s->cap) (void)hipStreamDestroy(s->cap);
@@ -552,7 +566,7 @@ static int create_solver(int nx, int ny, int precision, int with_polish, bool in
     s->d_first = reinterpret_cast<int*>(take(sizeof(int)));
     s->d_count = reinterpret_cast<int*>(take(sizeof(int)));
     take(sizeof(int));
-    s->d_result = reinterpret_cast<double*>(take(4 * 8));
+    take(4 * 8);
     s->d_guard = reinterpret_cast<RiseGuard*>(take(sizeof(RiseGuard)));
     s->d_items = reinterpret_cast<Item*>(take(s->max_items_ * sizeof(Item)));
     s->d_partial = reinterpret_cast<double*>(take(s->max_items_ * 3 * 8));
@@ -1053,8 +1067,6 @@ int solve_small(lbm_solver* s, double tol, long long max_steps, long long K,
         P.r_switch = (L.prec != LBM_FP64) ? s->r_switch : 0.0;
         P.nondec_in = nondec;
         hipError_t e = launch_solve_small(L.prec, L.general(), s->stream, P);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(s->h_result, s->d_result, 4 * 8, hipMemcpyDeviceToHost, s->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return s->hip_fail(e, "solve_to_tol");
         const long long m_new = (long long)s->h_result[0];
@@ -1140,8 +1152,6 @@ int lbm_solve_to_tol(lbm_solver* s, double tol, long long max_steps, int check_e
             inplace ? (j - n - (need_writeu ? 1 : 0)) : (need_writeu ? (j - 1 - n) : 0);
         const int span = s->check_launch_steps(nplain, need_writeu);
         hipError_t e = s->enqueue_chunk(nplain, need_writeu, true);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(s->h_result, s->d_result, 4 * 8, hipMemcpyDeviceToHost, s->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return s->hip_fail(e, "solve_to_tol");
         const double d2 = s->h_result[0], u2 = s->h_result[1], fm = s->h_result[2];
@@ -1207,8 +1217,6 @@ int lbm_step_checked(lbm_solver* s, long long nsteps, double* residual) {
     // two buffers: nsteps - 2 plain steps, a write-u step and the check step;
     // in place: the check launch does not step, so one plain step follows it
     hipError_t e = s->enqueue_chunk(nsteps - 2, true, true);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(s->h_result, s->d_result, 4 * 8, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return s->hip_fail(e, "step_checked");
     s->steps += s->L.inplace ? nsteps - 1 : nsteps;
@@ -1263,10 +1271,8 @@ int lbm_error_norms(lbm_solver* s, const double* ux_ref, const double* uy_ref, d
                                     uy_ref, s->d_red, s->stream);
     if (e != hipSuccess) return s->hip_fail(e, "error_norms");
     hipLaunchKernelGGL(k_reduce4<kErrMask>, dim3(1), dim3(kBlock), 0, s->stream, s->d_red,
-                       kErrBlocks, s->d_red + 4 * kErrBlocks);
-    if ((e = hipGetLastError()) == hipSuccess)
-        e = hipMemcpyAsync(s->h_result, s->d_red + 4 * kErrBlocks, 4 * 8, hipMemcpyDeviceToHost,
-                           s->stream);
+                       kErrBlocks, s->d_result);
+    e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return s->hip_fail(e, "error_norms");
     for (int c = 0; c < 4; ++c) out[c] = s->h_result[c];
@@ -1328,11 +1334,8 @@ int lbm_set_populations(lbm_solver* s, const double* f) {
         hipLaunchKernelGGL(k_force_stats, dim3(kErrBlocks), dim3(kBlock), 0, s->stream, f, f + h,
                            h, s->d_red);
         hipLaunchKernelGGL(k_reduce4<kForceMask>, dim3(1), dim3(kBlock), 0, s->stream, s->d_red,
-                           kErrBlocks, s->d_red + 4 * kErrBlocks);
+                           kErrBlocks, s->d_result);
         hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(s->h_result, s->d_red + 4 * kErrBlocks, 4 * 8,
-                               hipMemcpyDeviceToHost, s->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return s->hip_fail(e, "set_populations: max |f|");
         const double fmax = s->h_result[3];
@@ -1348,7 +1351,7 @@ int lbm_set_populations(lbm_solver* s, const double* f) {
     const double sc = d.gscale;
     hipError_t e;
     if (!s->L.inplace) {
-        e = set_f_measured(s->L.prec, d, s->sel(), f, sc, s->d_red, s->h_result, s->stream);
+        e = set_f_measured(s->L.prec, d, s->sel(), f, sc, s->d_red, s->d_result, s->stream);
     } else {  // no polish switch, no targets
         const int lay = s->L.layout(s->sel());
         if (s->L.prec == LBM_FP64) e = launch_set_f<double>(d, s->sel(), lay, f, sc, s->stream);

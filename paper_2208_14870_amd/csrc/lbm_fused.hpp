@@ -450,17 +450,20 @@ constexpr int kSquare = 32;
 
 struct SquareLaunch {
     const SlotDesc* slots;
-    int flip;     // launch parity: source buffer = buf[cur ^ flip]
-    int tiles_x;  // tiles per row
+    double* partial;  // 3 doubles per tile (check mode)
+    int flip;         // launch parity: source buffer = buf[cur ^ flip]
+    int tiles_x;      // tiles per row
 };
 
-template <typename S, int NS, bool SR = false, bool GEN = false>
+// MODE kPlain or kCheck (the last two steps form a residual check, as in k_stepN).
+template <typename S, int NS, int MODE = kPlain, bool SR = false, bool GEN = false>
 static __global__ __launch_bounds__(kSquare* kSquare) void k_stepS(SquareLaunch L) {
     using C = typename Store<S>::C;
     constexpr int T = kSquare - 2 * (NS - 1), NT = kSquare * kSquare;
     using Geo = SlotGeo<T, NS, NT, T>;
     static_assert(Geo::NM == 1 && Geo::RN == NT, "one site per thread");
     __shared__ S lds[8 * Geo::RN];
+    __shared__ double red[3 * (NT / kWave)];
     const SlotDesc& d = L.slots[0];
     // each XCD takes a contiguous range of the tiles (shared rows in one L2)
     const int n = (int)gridDim.x, b = (int)blockIdx.x;
@@ -481,9 +484,9 @@ static __global__ __launch_bounds__(kSquare* kSquare) void k_stepS(SquareLaunch 
     stepN_collide1<S, T, NS, NT, T, GEN>(f, k, lds, geo, gx, gy, qg, up, sid, sr,
                                          sr ? sr_step_hash(d.sr_step, d.sr_seed) : 0u);
     __syncthreads();
-    stepN_rest<S, T, NS, NT, kPlain, T, GEN>(reinterpret_cast<S*>(d.buf[sel ^ 1]), d.plane, d.nx,
-                                             d.ny, x0, y0, k, lds, geo, qg, up, nullptr, 1.0,
-                                             nullptr, nullptr, sid, sr, d.sr_step, d.sr_seed);
+    stepN_rest<S, T, NS, NT, MODE, T, GEN>(reinterpret_cast<S*>(d.buf[sel ^ 1]), d.plane, d.nx, d.ny,
+                                           x0, y0, k, lds, geo, qg, up, d.u, d.inv_scale,
+                                           L.partial + 3 * t, red, sid, sr, d.sr_step, d.sr_seed);
 }
 
 }  // namespace lbm

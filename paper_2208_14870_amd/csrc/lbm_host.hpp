@@ -296,37 +296,6 @@ inline hipError_t launch_stepN(int prec, int ns, int th, unsigned grid, hipStrea
     return hipGetLastError();
 }
 
-// One launch of ns steps (2..12) through the small-lattice kernel: tiles of
-// 32 - 2 (ns - 1) a side from the grid.
-template <typename S, bool SR, bool GEN, int NS = 2>
-inline bool launch_stepS_ns(int ns, unsigned grid, hipStream_t st, const SquareLaunch& L) {
-    if (ns == NS) {
-        hipLaunchKernelGGL((k_stepS<S, NS, SR, GEN>), dim3(grid), dim3(kSquare * kSquare), 0, st, L);
-        return true;
-    }
-    if constexpr (NS < 12) return launch_stepS_ns<S, SR, GEN, NS + 1>(ns, grid, st, L);
-    return false;
-}
-inline hipError_t launch_stepS(int prec, int ns, int nx, int ny, const SlotDesc* slots, int flip,
-                               hipStream_t st, bool sr, bool gen) {
-    if (ns < 2 || ns > 12 || (sr && gen)) return hipErrorInvalidValue;
-    const int t = kSquare - 2 * (ns - 1);
-    SquareLaunch L;
-    L.slots = slots;
-    L.flip = flip;
-    L.tiles_x = (nx + t - 1) / t;
-    const unsigned grid = (unsigned)L.tiles_x * (unsigned)((ny + t - 1) / t);
-    bool ok;
-    if (prec == LBM_FP64) ok = gen ? launch_stepS_ns<double, false, true>(ns, grid, st, L)
-                                   : launch_stepS_ns<double, false, false>(ns, grid, st, L);
-    else if (prec == LBM_FP32) ok = gen ? launch_stepS_ns<float, false, true>(ns, grid, st, L)
-                                        : launch_stepS_ns<float, false, false>(ns, grid, st, L);
-    else if (sr) ok = launch_stepS_ns<__half, true, false>(ns, grid, st, L);
-    else ok = gen ? launch_stepS_ns<__half, false, true>(ns, grid, st, L)
-                  : launch_stepS_ns<__half, false, false>(ns, grid, st, L);
-    return ok ? hipGetLastError() : hipErrorInvalidValue;
-}
-
 // Whole solves of small lattices in one workgroup (k_solve_small): the largest
 // lattices whose two population buffers fit in LDS.
 constexpr int kSmallMax64 = 1152, kSmallMax32 = 2304;
@@ -495,11 +464,6 @@ inline bool wave_auto(int prec, long long n, bool sr) {
 // 2.07 / 1.89 (four steps), 440^2 2.2 / 2.5 (three); FP32 64^2 1.22 / 0.66,
 // 240 x 200 1.38 / 0.79, 400^2 1.62 / 1.32; FP16 240 x 200 1.84 / 0.79; free
 // rates FP64 288^2 2.28 / 1.14.
-inline int square_tile(int ns) { return kSquare - 2 * (ns - 1); }
-inline long long square_tiles(int ns, int nx, int ny) {
-    const int t = square_tile(ns);
-    return (long long)((nx + t - 1) / t) * ((ny + t - 1) / t);
-}
 inline int square_depth(int nx, int ny, int cus) {
     for (int ns = 12; ns >= 4; --ns)
         if (square_tiles(ns, nx, ny) <= cus) return ns;
@@ -809,20 +773,17 @@ inline hipError_t zero_bytes(void* p, size_t bytes, hipStream_t st) {
 // Store a state f(n) given in the paper's order into a buffer in kLayPull and
 // measure its neutral modes (blocking): out[0..3] = staggered sums and their
 // force terms, out[4..5] = sum m10, sum m01.  scratch: 8 * kErrBlocks + 12
-// doubles of device memory; host: 8 pinned doubles.
+// doubles of device memory; out: 8 doubles of host memory that the GPU writes.
 inline hipError_t set_f_measured(int prec, const SlotDesc& d, int sel, const double* f, double scale,
-                                 double* scratch, double* host, hipStream_t st) {
+                                 double* scratch, double* out, hipStream_t st) {
     auto run = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(kErrBlocks), dim3(kBlock), 0, st, d, sel, f, scale, scratch);
     };
     if (prec == LBM_FP64) run(k_set_f_sums<double>);
     else if (prec == LBM_FP32) run(k_set_f_sums<float>);
     else run(k_set_f_sums<__half>);
-    double* out = scratch + 8 * kErrBlocks;
     hipLaunchKernelGGL(k_reduce8<0>, dim3(2), dim3(kBlock), 0, st, scratch, kErrBlocks, out);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(host, out, 8 * sizeof(double), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     return e;
 }

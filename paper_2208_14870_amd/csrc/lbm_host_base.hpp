@@ -42,6 +42,20 @@ int wave_blocks_per_cu(int prec, int ns, int v);
 
 inline bool is_half(int prec) { return prec == LBM_FP16; }
 
+// The small-lattice kernel (k_stepS): regions of kSquare x kSquare sites, tiles
+// of square_tile(ns) a side at ns steps per launch (2..12).  check: the last two
+// steps form a residual check, three partials per tile into `partial`.  sr: half
+// storage with stochastic rounding; gen: free relaxation rates (not with sr).
+// Defined in lbm_square.hip.
+constexpr int kSquareSide = 32;
+inline int square_tile(int ns) { return kSquareSide - 2 * (ns - 1); }
+inline long long square_tiles(int ns, int nx, int ny) {
+    const int t = square_tile(ns);
+    return (long long)((nx + t - 1) / t) * ((ny + t - 1) / t);
+}
+hipError_t launch_square(int prec, int ns, int nx, int ny, const SlotDesc* slots, int flip,
+                         double* partial, bool check, hipStream_t st, bool sr, bool gen);
+
 // In place (one buffer): the copies of ring columns and halo rows that a
 // launch of ns steps reads (k_wave_halo), in bytes: per strip boundary 2R
 // columns of every row, per segment boundary 2 ns rows of every column, eight

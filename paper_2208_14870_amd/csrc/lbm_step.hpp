@@ -195,15 +195,16 @@ struct FinalizeLaunch {
     const double* partial;
     double* result;     // 4 doubles per slot: sum d, sum s, max |f|, unused
     int nslots;
+    int items = -1;     // >= 0: the one slot's items (a launch off the work list)
 };
 
 static __global__ __launch_bounds__(kBlock) void k_finalize(FinalizeLaunch F) {
     __shared__ double lds[12];
     const int slot = blockIdx.x;
     if (slot >= F.nslots) return;
-    const int cnt = F.count[slot];
+    const int cnt = F.items >= 0 ? F.items : F.count[slot];
     if (cnt == 0) return;
-    const int f0 = F.first[slot];
+    const int f0 = F.items >= 0 ? 0 : F.first[slot];
     double a = 0.0, b = 0.0, m = 0.0;
     for (int i = threadIdx.x; i < cnt; i += kBlock) {
         a += F.partial[3 * (f0 + i) + 0];
