@@ -743,7 +743,11 @@ int lbm_batch_step(lbm_batch* b, long long nsteps, int check) {
     long long nl = 0;
     for (int p = 0; p < 3; ++p)
         if (b->grid_for(p)) nl += b->launches(p, nsteps, check != 0);
-    if (nl >= 4) {
+    // fused launches one by one, single steps from captured graphs (a graph starts
+    // 5 us late, and each new list of lattices would capture its own)
+    bool single = false;
+    for (int p = 0; p < 3; ++p) single = single || (b->grid_for(p) && b->tb[p] < 2);
+    if (single && nl >= 4) {
         std::vector<long long> key{nsteps, (check ? 1 : 0) | b->flips() << 1,
                                    b->tb[0] | b->tb[1] << 4 | b->tb[2] << 8,
                                    b->th[0] | b->th[1] << 6 | b->th[2] << 12};

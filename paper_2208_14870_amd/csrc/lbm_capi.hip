@@ -99,9 +99,9 @@ struct lbm_solver {
     bool user_state = false;
     int e_user = INT_MIN;  // INT_MIN: the state sets no bound (all zero)
     std::string err;
-    // captured chunks keyed by (plain steps, writeU/check kind, start parity,
-    // precision, rows per thread, general path, grid)
-    std::map<std::tuple<long long, int, int, int, int, int, int, unsigned>, hipGraphExec_t> graphs;
+    // captured chunks of single steps keyed by (plain steps, writeU/check kind,
+    // start parity, precision, rows per thread, grid)
+    std::map<std::tuple<long long, int, int, int, int, unsigned>, hipGraphExec_t> graphs;
 
     int fail(int code, const std::string& m) {
         err = m;
@@ -302,10 +302,13 @@ struct lbm_solver {
         return hipGetLastError();
     }
 
-    // Steps per captured graph of plain steps: about 64, whole launches.
-    long long graph_chunk() const {
-        return L.inplace ? 64 : std::max(1, 64 / depth()) * (long long)depth();
-    }
+    // Sequences of fused launches are enqueued one by one: each launch is longer
+    // (6 us and more) than the host takes to enqueue it (2.5 us), and a captured
+    // graph of them starts 5 us late (solve of 240 x 200 with a check every 100
+    // steps, us per step: FP64 1.26 from graphs, 1.18 direct; FP32 1.01, 0.93).
+    // Single steps, which are shorter, replay captured graphs of kGraphSteps.
+    static constexpr long long kGraphSteps = 64;
+    bool blocked() const { return plan.wave || plan.square || L.fused(); }
 
     // Launches of np plain steps (two buffers), see next_span.
     long long plain_launches(long long np) const {
@@ -395,30 +398,21 @@ struct lbm_solver {
     // Steps of the launch that ends enqueue_chunk(nplain, writeu, true) (the
     // check launch): a fused check launch's span, else 1.
     int check_launch_steps(long long nplain, bool writeu) const {
-        const long long rest = nplain % graph_chunk();
-        const int span = writeu ? check_span(rest + 2) : 0;
+        const int span = writeu ? check_span(nplain + 2) : 0;
         return span ? span : 1;
     }
 
-    // Enqueue a chunk; long runs are replayed from captured graphs.  In place
-    // with blocked launches, a graph from kLayNatural holds 63 steps (an odd
-    // launch, then even ones) and one from kLaySwapped 64, so that whole
-    // graphs need no single step to restore the layout's parity.
+    // Enqueue a chunk (see kGraphSteps).
     hipError_t enqueue_chunk(long long nplain, bool writeu, bool check) {
         hipError_t e;
-        while (true) {
-            long long chunk = graph_chunk();
-            if (L.ip_blocked() && L.layout(sel()) == kLayNatural) chunk = 63;
-            if (nplain < chunk) break;
-            if ((e = run_graph(chunk, false, false)) != hipSuccess) return e;
-            nplain -= chunk;
-        }
-        if (nplain > 0 || writeu || check) {
+        if (!blocked()) {
+            for (; nplain >= kGraphSteps; nplain -= kGraphSteps)
+                if ((e = run_graph(kGraphSteps, false, false)) != hipSuccess) return e;
             if (launches(nplain, writeu, check) >= 4) return run_graph(nplain, writeu, check);
-            long long ph = phase;
-            if ((e = enqueue_seq(nplain, writeu, check, stream, ph)) != hipSuccess) return e;
-            phase = ph;
         }
+        long long ph = phase;
+        if ((e = enqueue_seq(nplain, writeu, check, stream, ph)) != hipSuccess) return e;
+        phase = ph;
         return hipSuccess;
     }
 
@@ -426,10 +420,7 @@ struct lbm_solver {
         const int flip0 = (int)(phase & 1);
         const int kind = (writeu ? 1 : 0) | (check ? 2 : 0) | (L.general() ? 4 : 0) |
                          (L.inplace ? 8 : 0) | (L.sr_on() ? 16 : 0);
-        const int shape = depth() | (L.th << 4) | (plan.wave ? 1 << 10 | plan.v << 11 : 0) |
-                          (plan.square ? 1 << 13 : 0);
-        auto key = std::make_tuple(nplain, kind, flip0 ^ (L.cur << 1), L.prec, L.eff_vy(), shape,
-                                   plan.wave ? plan.hs : 0, grid);
+        auto key = std::make_tuple(nplain, kind, flip0 ^ (L.cur << 1), L.prec, L.eff_vy(), grid);
         auto it = graphs.find(key);
         hipError_t e;
         if (it == graphs.end()) {
