@@ -448,7 +448,7 @@ const char *lbm_last_error(const lbm_solver *s);
  * list of their (lattice, strip, segment) workgroups, one column per lane, beside
  * the tile launch of the others.  By default (see
  * lbm_batch_set_wavefront_sites) these are, per storage type, all of its
- * lattices once they hold at least 2^22 (FP64), 2^23 (FP32) or 2^24 (FP16)
+ * lattices once they hold at least 200000 (FP64), 300000 (FP32) or 2^21 (FP16)
  * sites together, and otherwise those a single solver would step through the
  * register wavefront (FP32 from 2^20 sites, FP64 from 458752, FP16 from
  * 2^24).  A precision with lattices on the list defaults to eight steps per

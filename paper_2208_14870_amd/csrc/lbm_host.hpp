@@ -344,15 +344,16 @@ inline bool wave_by_default(int prec, long long n) {
            (prec == LBM_FP16 && n >= (1LL << 24));
 }
 // In a batch, lattices of one storage type fill the chip together, so above
-// these totals every lattice of the type takes the wavefront list (GLUPS at
-// eight steps, tile / wavefront list, 2000 steps in checked chunks of 100:
-// FP64 512 lattices of sides 64..512 (43.9 M sites) 112 / 199, 8 x 1024^2
-// 104 / 182, 64 lattices 256..512 (12.4 M) 116 / 162, 512 lattices 64..128
-// (5.3 M) 108 / 140, 16 lattices 128..256 (0.74 M) 92 / 78; FP32 in the same
-// order 272 / 316, 267 / 308, 279 / 268, 249 / 223, 187 / 124; FP16 43.9 M
-// 358 / 381).  Below them only the lattices of wave_by_default do.
+// these totals every lattice of the type takes the wavefront list (us per step,
+// tile kernel / wavefront list: FP64 16 lattices 48..256 (0.32 M sites) 3.93 /
+// 2.73, 8 of 48..128 (0.09 M) 1.76 / 2.59, 128 of 48..128 (1.1 M) 12.8 / 8.8, 256
+// of 64..512 (18 M) 163 / 72; FP32 32 of 48..128 (0.28 M) 2.39 / 2.41, 16 of
+// 48..256 (0.32 M) 2.51 / 2.25, 128 of 48..128 6.01 / 5.02, 256 of 64..512 62.7 /
+// 41.5; FP16 128 of 48..128 5.20 / 5.19, 64 of 64..256 (1.5 M) 5.98 / 6.16, 32 of
+// 100..512 (2.2 M) 7.75 / 6.86, 256 of 64..512 51.7 / 42.6).  Below them only the
+// lattices of wave_by_default do.
 inline long long batch_wave_total(int prec) {
-    return prec == LBM_FP64 ? (1LL << 22) : prec == LBM_FP32 ? (1LL << 23) : (1LL << 24);
+    return prec == LBM_FP64 ? 200000 : prec == LBM_FP32 ? 300000 : (1LL << 21);
 }
 struct FusedChoice {
     int wave_hs = 0, wave_v = 1;
