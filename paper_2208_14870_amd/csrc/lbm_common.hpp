@@ -63,9 +63,11 @@ struct Item {
 };
 
 // ---------------------------------------------------------------------------
-// storage traits.  Every population is read once and written once per step,
-// so loads and stores carry the non-temporal hint (measured on MI355X: best
-// for both cache-resident and HBM-resident lattices).
+// storage traits.  A single step reads every population once and writes it
+// once, so its loads (ld) and all stores carry the non-temporal hint.  Fused
+// launches read the ring around a tile or strip several times, on one XCD at
+// about the same time; their loads (ld_shared) do not carry it (us per step with
+// / without: FP64 400^2 1.93 / 1.56, FP32 64^2 0.60 / 0.53, 4096^2 34.9 / 31.6).
 // ---------------------------------------------------------------------------
 //
 // Pointers taken from a descriptor in memory are generic, and the compiler
@@ -84,6 +86,7 @@ template <> struct Store<double> {
     __device__ static __forceinline__ C ld(const double* p) {
         return __builtin_nontemporal_load(glob(p));
     }
+    __device__ static __forceinline__ C ld_shared(const double* p) { return *glob(p); }
     __device__ static __forceinline__ void st(double* p, C v) {
         __builtin_nontemporal_store(v, glob(p));
     }
@@ -93,6 +96,7 @@ template <> struct Store<float> {
     __device__ static __forceinline__ C ld(const float* p) {
         return __builtin_nontemporal_load(glob(p));
     }
+    __device__ static __forceinline__ C ld_shared(const float* p) { return *glob(p); }
     __device__ static __forceinline__ void st(float* p, C v) {
         __builtin_nontemporal_store(v, glob(p));
     }
@@ -102,6 +106,7 @@ template <> struct Store<__half> {
     __device__ static __forceinline__ C ld(const __half* p) {
         return __half2float(__ushort_as_half(*glob(reinterpret_cast<const unsigned short*>(p))));
     }
+    __device__ static __forceinline__ C ld_shared(const __half* p) { return ld(p); }
     __device__ static __forceinline__ void st(__half* p, C v) {
         __half h = __float2half_rn(v);
         __builtin_nontemporal_store(__half_as_ushort(h), glob(reinterpret_cast<unsigned short*>(p)));

@@ -174,14 +174,14 @@ __device__ __forceinline__ void stepN_load(const S* __restrict__ src,
             const unsigned c = base + (unsigned)geo.j(a) * w + (unsigned)geo.i(a);
             const unsigned cm = c - w, cp = c + w;
             // pull: f_q(x) = f*_q(x - c_q), velocity table order
-            f[a][0] = Store<S>::ld(at_u32(pq[0], c - 1));
-            f[a][1] = Store<S>::ld(at_u32(pq[1], cm));
-            f[a][2] = Store<S>::ld(at_u32(pq[2], c + 1));
-            f[a][3] = Store<S>::ld(at_u32(pq[3], cp));
-            f[a][4] = Store<S>::ld(at_u32(pq[4], cm - 1));
-            f[a][5] = Store<S>::ld(at_u32(pq[5], cm + 1));
-            f[a][6] = Store<S>::ld(at_u32(pq[6], cp + 1));
-            f[a][7] = Store<S>::ld(at_u32(pq[7], cp - 1));
+            f[a][0] = Store<S>::ld_shared(at_u32(pq[0], c - 1));
+            f[a][1] = Store<S>::ld_shared(at_u32(pq[1], cm));
+            f[a][2] = Store<S>::ld_shared(at_u32(pq[2], c + 1));
+            f[a][3] = Store<S>::ld_shared(at_u32(pq[3], cp));
+            f[a][4] = Store<S>::ld_shared(at_u32(pq[4], cm - 1));
+            f[a][5] = Store<S>::ld_shared(at_u32(pq[5], cm + 1));
+            f[a][6] = Store<S>::ld_shared(at_u32(pq[6], cp + 1));
+            f[a][7] = Store<S>::ld_shared(at_u32(pq[7], cp - 1));
             gx[a] = *glob(at_u32(g, c));
             gy[a] = *glob(at_u32(g1, c));
             if constexpr (SR) sid[a] = c;
@@ -197,14 +197,14 @@ __device__ __forceinline__ void stepN_load(const S* __restrict__ src,
         const unsigned ym = (y == 0) ? (unsigned)ny - 1 : y - 1;
         const unsigned yp = (y == (unsigned)ny - 1) ? 0 : y + 1;
         const unsigned r0 = y * w, rm = ym * w, rp = yp * w;
-        f[a][0] = Store<S>::ld(at_u32(pq[0], r0 + xm));
-        f[a][1] = Store<S>::ld(at_u32(pq[1], rm + x));
-        f[a][2] = Store<S>::ld(at_u32(pq[2], r0 + xp));
-        f[a][3] = Store<S>::ld(at_u32(pq[3], rp + x));
-        f[a][4] = Store<S>::ld(at_u32(pq[4], rm + xm));
-        f[a][5] = Store<S>::ld(at_u32(pq[5], rm + xp));
-        f[a][6] = Store<S>::ld(at_u32(pq[6], rp + xp));
-        f[a][7] = Store<S>::ld(at_u32(pq[7], rp + xm));
+        f[a][0] = Store<S>::ld_shared(at_u32(pq[0], r0 + xm));
+        f[a][1] = Store<S>::ld_shared(at_u32(pq[1], rm + x));
+        f[a][2] = Store<S>::ld_shared(at_u32(pq[2], r0 + xp));
+        f[a][3] = Store<S>::ld_shared(at_u32(pq[3], rp + x));
+        f[a][4] = Store<S>::ld_shared(at_u32(pq[4], rm + xm));
+        f[a][5] = Store<S>::ld_shared(at_u32(pq[5], rm + xp));
+        f[a][6] = Store<S>::ld_shared(at_u32(pq[6], rp + xp));
+        f[a][7] = Store<S>::ld_shared(at_u32(pq[7], rp + xm));
         gx[a] = *glob(at_u32(g, r0 + x));
         gy[a] = *glob(at_u32(g1, r0 + x));
         if constexpr (SR) sid[a] = r0 + x;

@@ -73,13 +73,13 @@ __device__ __forceinline__ float as_stored<__half>(float v) { return __half2floa
 template <typename S, int V> struct VecIO;
 template <typename S> struct VecIO<S, 1> {
     using C = typename Store<S>::C;
-    __device__ static __forceinline__ void ld(const S* p, C o[1]) { o[0] = Store<S>::ld(p); }
+    __device__ static __forceinline__ void ld(const S* p, C o[1]) { o[0] = Store<S>::ld_shared(p); }
     __device__ static __forceinline__ void st(S* p, const C v[1]) { Store<S>::st(p, v[0]); }
 };
 typedef float wf2 __attribute__((ext_vector_type(2)));
 template <> struct VecIO<float, 2> {
     __device__ static __forceinline__ void ld(const float* p, float o[2]) {
-        const wf2 v = __builtin_nontemporal_load(glob(reinterpret_cast<const wf2*>(p)));
+        const wf2 v = *glob(reinterpret_cast<const wf2*>(p));
         o[0] = v.x;
         o[1] = v.y;
     }
@@ -92,7 +92,7 @@ template <> struct VecIO<float, 2> {
 };
 template <> struct VecIO<__half, 2> {
     __device__ static __forceinline__ void ld(const __half* p, float o[2]) {
-        const unsigned u = __builtin_nontemporal_load(glob(reinterpret_cast<const unsigned*>(p)));
+        const unsigned u = *glob(reinterpret_cast<const unsigned*>(p));
         o[0] = __half2float(__ushort_as_half((unsigned short)(u & 0xffffu)));
         o[1] = __half2float(__ushort_as_half((unsigned short)(u >> 16)));
     }
