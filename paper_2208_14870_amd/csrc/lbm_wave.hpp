@@ -380,10 +380,17 @@ __device__ __forceinline__ void wave_group(const WaveLaunch& L, const SlotDesc& 
         }
     };
     for (int i = 0; i < i0; ++i) wave_barrier();
+    int wr = 0;  // rho within the lattice (stochastic rounding)
+    if constexpr (kSR) {
+        static_assert(NL <= 2, "the wrap of rho - l");
+        wr = wrap_coord(ya - NS + i0 - lag, ny);
+    }
     for (int ib = i0; ib < iend; ib += 8) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             if (ib + u >= iend) break;
+            if constexpr (kSR)
+                if (ib + u > i0 && ++wr == ny) wr = 0;
             const int rho = ya - NS + ib + u - lag;  // row of the group's first level
             auto from_left = [&](const C(*row)[V], int q, int c) {
                 return c > 0 ? row[q][c - 1] : lane_from_left(row[q][V - 1]);
@@ -449,7 +456,8 @@ __device__ __forceinline__ void wave_group(const WaveLaunch& L, const SlotDesc& 
                     collide_q<C, GEN>(f[c], Q[(u + 8 - l) % 8][0][c], Q[(u + 8 - l) % 8][1][c], k, ux, uy);
                 }
                 if constexpr (kSR) {
-                    const unsigned row = (unsigned)wrap_coord(rho - l, ny) * (unsigned)nx;
+                    // (l is 0 or 1, so one wrap is enough for any ny)
+                    const unsigned row = (unsigned)(wr < l ? wr - l + ny : wr - l) * (unsigned)nx;
 #pragma unroll
                     for (int c = 0; c < V; ++c) {
                         SrBits sb;
