@@ -55,7 +55,7 @@ PEAK_VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
 
 # the headers that define each fused kernel family
 TRAFFIC_SOURCES = {"tile": ("lbm_common.hpp", "lbm_fused.hpp"),
-                   "wave": ("lbm_common.hpp", "lbm_wave.hpp")}
+                   "wave": ("lbm_common.hpp", "lbm_wave_shape.hpp", "lbm_wave.hpp")}
 
 
 def kernel_family(kernel: str) -> str:
@@ -201,13 +201,13 @@ def parse():
                     help="run only the two serving legs (overloaded, then sustained)")
     ap.add_argument("--headline-kernel", choices=("default", "tile"), default="default",
                     help="fused kernel of the 1024^2 FP32 headline: the library's default "
-                         "(the register wavefront) or the LDS tile kernel, for comparison")
+                         "(the wavefront) or the LDS tile kernel, for comparison")
     ap.add_argument("--large-steps", type=int, default=10000)
     ap.add_argument("--large-warm", type=int, default=200)
     ap.add_argument("--large-tb", type=int, default=0,
                     help="steps per launch of the 8192^2 runs (0: library default, "
-                         "the register wavefront at eight steps; the default kernel is "
-                         "kept at other depths)")
+                         "the wavefront at twelve steps, eight for FP16; the default "
+                         "kernel is kept at other depths)")
     return ap.parse_args()
 
 
@@ -234,10 +234,19 @@ def make_solvers(cases, prec, kernel="default"):
     return out
 
 
-def kernel_label(cfg, ctype, sites, sr=False):
+def plain_depth(cfg, ctype, chosen=False):
+    """Steps per launch of plain steps: the launch config's when the caller
+    chose it, else the library's own depth where the wavefront is the default
+    (twelve for FP64 and FP32)."""
+    if chosen or cfg["kernel"] != "wavefront" or ctype == "__half":
+        return cfg["steps_per_launch"]
+    return 12
+
+
+def kernel_label(cfg, ctype, sites, sr=False, chosen=False):
     """Name (with its full template arguments, as the profiler names it) and
     algorithmic traffic of the plain-step kernel of a launch config."""
-    tb, rows, nt = cfg["steps_per_launch"], cfg["rows"], cfg["threads"]
+    tb, rows, nt = plain_depth(cfg, ctype, chosen), cfg["rows"], cfg["threads"]
     per_site = {"double": 144, "float": 72, "__half": 40}[ctype]
     side = int(round(math.sqrt(sites)))
     srs = "true" if sr else "false"
@@ -247,8 +256,8 @@ def kernel_label(cfg, ctype, sites, sr=False):
                 f"site-update algorithmic, {tb} x {side}^2 site-updates per launch")
     if cfg["kernel"] == "wavefront":  # type, steps, columns per lane, rounding, in place, work list
         v = cfg.get("columns_per_lane", 1)
-        return (f"k_wave<{ctype}, {tb}, {v}, {srs}, false, false> (register wavefront, {rows}-row "
-                f"segments): {tb} fused steps per launch, "
+        return (f"k_wave<{ctype}, {tb}, {v}, {srs}, false, false, false> (wavefront over the waves "
+                f"of a workgroup): {tb} fused steps per launch, "
                 f"{per_site} B per site-update algorithmic, {tb} x {side}^2 site-updates per launch")
     return f"k_step<{ctype}, ...>: one step per launch, {per_site} B per site-update algorithmic"
 
@@ -263,7 +272,8 @@ def run_workload(solvers, nchunks, chunk):
     ev = []
     last = []
     history = []  # residual of the first case after every chunk
-    tb = solvers[0][0].launch_config()["steps_per_launch"]
+    first = solvers[0][0]
+    tb = min(plain_depth(first.launch_config(), ""), max(2, chunk // 2))
     checked = max(2, tb)  # the chunk's last launch carries the residual check
     per = chunk - checked
     fused, rest = per - per % tb, per % tb
@@ -439,13 +449,13 @@ def large_lattice(steps=10000, warm=200, precs=("fp64", "fp32", "fp16", "fp16sr"
         del ux, uy
         s.close()
         del s
-        tbl = cfg["steps_per_launch"]
-        launches = steps // tbl + (1 if steps % tbl else 0)
         ctype = {"fp64": "double", "fp32": "float", "fp16": "__half"}[prec]
+        tbl = plain_depth(cfg, ctype, bool(tb))
+        launches = steps // tbl + (1 if steps % tbl else 0)
         out[key] = {"mlups": round(sites / us, 1), "us_per_step": round(us, 2),
                     "launch_config": cfg,
                     "roofline": roofline(prec, sites, us * steps / launches, tbl,
-                                         kernel_label(cfg, ctype, sites, key == "fp16sr"),
+                                         kernel_label(cfg, ctype, sites, key == "fp16sr", bool(tb)),
                                          (f"k_stepN_{prec}_8192_counters" if cfg["kernel"] == "tile"
                                           else f"k_wave_{prec}_8192_counters")
                                          if key == prec else None)}

@@ -392,8 +392,9 @@ enum lbm_fused_kernel {
 
 /* Select the fused kernel for steps_per_launch >= 2.  segment_rows (1..2^20)
  * is used by LBM_FUSED_WAVEFRONT only: each strip is split into segments of
- * that many rows, each recomputing 2k halo rows.  Default (until this is
- * called, and again after a polish switch), measured: the wavefront for FP64
+ * that many rows, each recomputing 2k halo rows.  Nominal default (until this is
+ * called, and again after a polish switch; what lbm_get_launch_config reports):
+ * the wavefront for FP64
  * lattices from 458752 sites (about 677^2), FP32 from 2^20 (two columns per
  * lane from 2^25 on even widths) and FP16 from 2^24, with segments as long as
  * leaves one wave per SIMD over the lattice's strips (16 to 128 rows); the
@@ -449,11 +450,10 @@ const char *lbm_last_error(const lbm_solver *s);
  * the tile launch of the others.  By default (see
  * lbm_batch_set_wavefront_sites) these are, per storage type, all of its
  * lattices once they hold at least 200000 (FP64), 300000 (FP32) or 2^21 (FP16)
- * sites together, and otherwise those a single solver would step through the
- * register wavefront (FP32 from 2^20 sites, FP64 from 458752, FP16 from
- * 2^24).  A precision with lattices on the list defaults to eight steps per
- * launch.  Residual checks run through the tile kernel for every lattice.
- * Results are identical either way (each equals single steps). */
+ * sites together, and otherwise the large ones (FP32 from 2^20 sites, FP64 from
+ * 458752, FP16 from 2^24).  A precision with lattices on the list defaults to
+ * eight steps per launch.  Residual checks run through the tile kernel for every
+ * lattice.  Results are identical either way (each equals single steps). */
 
 /* Bytes of arena one lattice occupies in a batch at `precision` (with
  * `with_polish`: plus its FP64 polish state).  Used for admission. */

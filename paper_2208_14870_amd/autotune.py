@@ -2,9 +2,8 @@
 
 Times candidate launch shapes (tile width, rows per thread, persistent grid
 or one workgroup per tile, steps per launch, and for a single lattice the
-fused kernel: LDS tile with its tile height or register wavefront with its
-segment height) with
-HIP events on the solver's stream and keeps the fastest.  Results are cached in a JSON file keyed by GPU architecture,
+fused kernel: LDS tile with its tile height or wavefront with its segment
+height) with HIP events on the solver's stream and keeps the fastest.  Results are cached in a JSON file keyed by GPU architecture,
 storage precision, workload kind and a size bucket (log2 of the sites per
 step), so a shape is measured once per machine and size class.
 

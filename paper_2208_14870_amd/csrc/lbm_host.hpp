@@ -318,8 +318,11 @@ inline hipError_t launch_solve_small(int prec, bool general, hipStream_t st, con
     return hipGetLastError();
 }
 
-// Default fused kernel of a single lattice of N = nx ny sites, measured on
-// MI355X (GLUPS at eight steps per launch, kernel alone; FP64 tile at five):
+// Nominal fused kernel of a single lattice of N = nx ny sites: the shape that
+// lbm_get_launch_config reports and the set calls start from; while none has
+// been called, plain steps run by wave_auto and square_depth instead.  The
+// line was drawn with the wavefront of one wave per strip (GLUPS on MI355X at
+// eight steps per launch, kernel alone; FP64 tile at five):
 //   FP32  tile / wavefront: 1024^2 242 / 246 (checked chunks of 1000 steps;
 //         segments of 22 rows give 1034 waves, a second round: 160), 1100^2
 //         212 / 271, 1448^2 231 / 333, 2048^2 239 / 399, 4096^2 263 / 377,
@@ -460,10 +463,10 @@ inline bool wave_auto(int prec, long long n, bool sr) {
 // compute units, 0 when there is none.  Its launches are chains of latencies
 // (FP64 about 5.5 us and 0.4 us per step, FP32 4.3 and 0.3), so a second
 // workgroup on a compute unit costs more than a shallower launch.  Measured, us
-// per step, 64-wide tile or wavefront / this kernel: FP64 64^2 1.52 / 0.86,
-// 240 x 200 1.62 / 1.06 (nine steps; ten, on 300 tiles, 1.33), 400^2
-// 2.07 / 1.89 (four steps), 440^2 2.2 / 2.5 (three); FP32 64^2 1.22 / 0.66,
-// 240 x 200 1.38 / 0.79, 400^2 1.62 / 1.32; FP16 240 x 200 1.84 / 0.79; free
+// per step, 64-wide tile or wavefront / this kernel: FP64 64^2 1.52 / 0.71,
+// 240 x 200 1.62 / 0.93 (nine steps; ten, on 300 tiles, 1.33 against 1.06 then),
+// 400^2 2.07 / 1.56 (four steps), 440^2 2.2 / 2.5 (three); FP32 64^2 1.22 / 0.53,
+// 240 x 200 1.38 / 0.66, 400^2 1.62 / 1.19; FP16 240 x 200 1.84 / 0.68; free
 // rates FP64 288^2 2.28 / 1.14.
 inline int square_depth(int nx, int ny, int cus) {
     for (int ns = 12; ns >= 4; --ns)

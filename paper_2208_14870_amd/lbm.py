@@ -370,7 +370,7 @@ class Solver:
         self._check(self.lib.lbm_set_stochastic_rounding(self.h, 1 if on else 0, int(seed) & 0xffffffff))
 
     def set_fused_kernel(self, kind: str, segment_rows: int = 256):
-        """kind "tile" (LDS tile kernel) or "wavefront" (register wavefront with
+        """kind "tile" (LDS tile kernel) or "wavefront" (levels in registers, with
         segments of `segment_rows` rows); see lbm_set_fused_kernel."""
         k = {"tile": 0, "wavefront": 1}[kind]
         self._check(self.lib.lbm_set_fused_kernel(self.h, k, int(segment_rows)))
