@@ -167,7 +167,8 @@ struct lbm_solver {
         }
         plan.wave = true;
         plan.ns = depth_auto && fused_auto ? wave_depth(prec) : L.tb;
-        plan.v = wave_cols(prec, plan.ns, L.nx, L.ny);
+        plan.v = depth_auto && fused_auto && !gen ? wave_cols_deep(prec, L.nx, L.ny)
+                                                  : wave_cols(prec, plan.ns, L.nx, L.ny);
         const int w = wave_out(plan.ns, plan.v, is_half(prec));
         const long long strips = (L.nx + w - 1) / w;
         plan.hs = fused_auto ? wave_segment_rows(plan.ns, cus, wave_blocks_per_cu(prec, plan.ns, plan.v),

@@ -424,7 +424,9 @@ struct PlainPlan {
 // per row, two 0.43, three 0.54), so long segments in few rounds compete with
 // short ones that fill the chip.  Measured against fixed heights: FP64
 // 1023 x 770 193 GLUPS at 36 rows (one round of 242 workgroups), 120 at 31 (a
-// second round of 19); 4096^2 303 at 256, 267 at 128.
+// second round of 19).  A sweep of 36 heights over 17 lattices of 400^2 to
+// 8192^2 found none more than 3 % faster than this one (FP64 4096^2 396 GLUPS at
+// 683 rows, 353 at 342; FP32 2048^2 553 at 86, 535 at 90).
 template <typename F>
 inline int wave_segment_rows(int ns, int cus, int per_cu, int lo, int ny, F&& groups) {
     int best = std::max(lo, 1);
@@ -474,6 +476,15 @@ inline int square_depth(int nx, int ny, int cus) {
     return 0;
 }
 inline int wave_depth(int prec) { return prec == LBM_FP16 ? 8 : 12; }
+// Columns per lane of the wavefront at that depth: two for FP32 on even widths
+// from 12 M sites, where the lattice no longer fits the caches and fewer loads
+// per site (two columns in one access, ring of 24 per 104 columns instead of per
+// 98) outweigh the fewer waves (us per step, one / two columns:
+// 3000^2 15.1 / 15.6, 4096 x 3000 21.9 / 21.4, 4096^2 29.8 / 28.2, 4600^2
+// 36.7 / 34.0, 8192^2 117 / 103; 2048^2 7.5 / 8.4).
+inline int wave_cols_deep(int prec, int nx, int ny) {
+    return prec == LBM_FP32 && nx % 2 == 0 && (long long)nx * ny >= 12000000 ? 2 : 1;
+}
 
 // Default steps per launch for `sites` lattice sites (of one lattice, or of
 // all lattices of one storage type in a batch), measured on MI355X: the LDS

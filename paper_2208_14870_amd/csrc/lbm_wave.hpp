@@ -37,9 +37,9 @@ namespace lbm {
 // large lattices are bound by HBM, 2 x 8 populations and two force values per
 // NS steps), and a segment is four times as long for the same number of waves.
 // Measured on MI355X (GLUPS of plain launches, one wave per strip at eight
-// levels / this kernel): FP32 1024^2 239 / 309, 8192^2 441 / 596; FP64
-// 1023 x 770 126 / 200, 4096^2 232 / 303; FP16 8192^2 446 / 546, with
-// stochastic rounding 4096^2 216 / 299.
+// levels / this kernel): FP32 1024^2 239 / 318, 8192^2 441 / 639; FP64
+// 1023 x 770 126 / 208, 4096^2 232 / 396; FP16 4096^2 387 / 556, with
+// stochastic rounding 216 / 316.
 //
 // The shifts write 0 where no source lane exists (lane 0 from the left, lane 63
 // from the right: ring lanes whose values never reach the output), so the

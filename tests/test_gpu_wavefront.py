@@ -71,9 +71,17 @@ def test_default_depth_equals_single_steps(prec, nx, ny):
 
 
 def test_default_depth_two_columns_per_lane():
-    """FP32 from 2^25 sites on an even width: two columns per lane."""
+    """A large FP32 lattice on an even width: two columns per lane."""
     say("default depth fp32 5826x5780")
     _pair(5826, 5780, "fp32", steps=(12, 5))
+
+
+@pytest.mark.parametrize("nx,ny", [(4000, 3000), (4002, 2998)])
+def test_default_depth_columns_per_lane_at_the_line(nx, ny):
+    """FP32 at 12 M sites (two columns per lane) and just below (one), a full
+    launch and remainders of one and two launches."""
+    say(f"default depth fp32 {nx}x{ny}")
+    _pair(nx, ny, "fp32", steps=(12, 5, 10))
 
 
 def test_default_depth_stochastic_rounding():
