@@ -229,7 +229,8 @@ struct lbm_solver {
         return a;
     }
 
-    // After a launch of ns steps: advance the device's stochastic-rounding step.
+    // After a launch of ns steps: advance the device's stochastic-rounding step
+    // (negative: a launch that is taken back).
     hipError_t advance_sr(int ns, hipStream_t st) {
         if (!L.sr_on()) return hipSuccess;
         hipLaunchKernelGGL(k_add_sr_step, dim3(1), dim3(1), 0, st, d_desc, ns);
@@ -1163,14 +1164,15 @@ int lbm_solve_to_tol(lbm_solver* s, double tol, long long max_steps, int check_e
             if (!inplace) {
                 // the check launch advanced to j + 1 and its source buffer still
                 // holds the state it started from, f(j + 1 - span): take the
-                // launch back and advance the span - 1 steps to f(j) again
+                // launch back, with the steps it counted for the stochastic
+                // rounding, and advance the span - 1 steps to f(j) again
                 s->phase -= 1;
                 s->steps -= span;
-                if (span > 1) {
-                    hipError_t e2 = s->enqueue_chunk(span - 1, false, false);
-                    if (e2 != hipSuccess) return s->hip_fail(e2, "solve_to_tol");
-                    s->steps += span - 1;
-                }
+                hipError_t e2 = s->advance_sr(-span, s->stream);
+                if (e2 == hipSuccess && span > 1)
+                    e2 = s->enqueue_chunk(span - 1, false, false);
+                if (e2 != hipSuccess) return s->hip_fail(e2, "solve_to_tol");
+                s->steps += span - 1;
             }
             n = j;
             *steps_done = n;

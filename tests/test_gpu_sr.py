@@ -74,6 +74,48 @@ def test_sr_fused_identical_to_single_steps(nx, ny, steps):
     assert not np.array_equal(other, ref[0])
 
 
+@pytest.mark.parametrize("nx,ny", [(100, 72), (64, 16), (33, 65), (300, 200)])
+@pytest.mark.parametrize("steps,K", [(12, 6), (6, 6), (10, 5), (3, 3), (4, 1)])
+def test_sr_solve_that_stops_on_a_check_keeps_the_steps_bits(nx, ny, steps, K):
+    """A solve whose last step is a check takes the check launch back and
+    repeats its steps: the state is that of as many plain steps, and so are the
+    states of the steps after it, for every kernel and the library's default."""
+    say(f"stochastic rounding solve {nx}x{ny} steps {steps} check {K}")
+    mat = P.Material.from_shear_poisson(0.8, 0.3)
+    gx, gy = _load(nx, ny, 5 + nx, mat)
+    # a uniform displacement (conserved) with noise: the largest population stays
+    # inside the window of the half scale, so that no check rescales the state
+    rng = np.random.default_rng(nx)
+    f0 = 0.05 * rng.uniform(-1.0, 1.0, (8, ny, nx))
+    for q, v in ((0, 0.6), (2, -0.6), (4, 0.2), (5, -0.2), (6, -0.2), (7, 0.2)):
+        f0[q] += v
+
+    def run(tb, kind, solve):
+        s = _solver(nx, ny)
+        _setup(s, mat, gx * 1e-3, gy * 1e-3)
+        s.set_populations(dev(f0))
+        s.set_stochastic_rounding(True, 1234)
+        if tb:
+            s.set_time_blocking(tb)
+            s.set_fused_kernel(kind, 16)
+        s.step(7)
+        if solve:
+            n, _, _ = s.solve_to_tol(0.0, steps, K)
+            assert n == steps
+        else:
+            s.step(steps)
+        a = host(s.populations())
+        s.step(9)
+        b = host(s.populations())
+        s.close()
+        return a, b
+
+    ref = run(1, "tile", False)
+    for tb, kind in [(0, None), (1, "tile")] + [(t, k) for t in (2, 5, 8) for k in ("tile", "wavefront")]:
+        got = run(tb, kind, True)
+        np.testing.assert_array_equal(got[0], ref[0], err_msg=f"after the solve: {tb} {kind}")
+        np.testing.assert_array_equal(got[1], ref[1], err_msg=f"nine steps on: {tb} {kind}")
+
 def test_sr_rerun_and_reset_repeat():
     """A second run after lbm_reset, and a second solver, give the same bits;
     switching the rounding off gives round-to-nearest again."""
