@@ -849,11 +849,11 @@ int lbm_batch_promote(lbm_batch* b, int slot) {
     const long long n = 8 * L.plane;
     const double factor = (L.prec == LBM_FP16) ? std::ldexp(1.0, L.e_scale) : 1.0;
     if (L.prec == LBM_FP32)
-        hipLaunchKernelGGL((k_recast<float, double>), dim3(blocks_for(n)), dim3(kBlock), 0,
+        hipLaunchKernelGGL((k_recast<float, double>), dim3(stride_blocks_for(n)), dim3(kBlock), 0,
                            b->stream, reinterpret_cast<const float*>(L.mem.buf[sl]),
                            reinterpret_cast<double*>(L.mem.pbuf[0]), n, factor);
     else
-        hipLaunchKernelGGL((k_recast<__half, double>), dim3(blocks_for(n)), dim3(kBlock), 0,
+        hipLaunchKernelGGL((k_recast<__half, double>), dim3(stride_blocks_for(n)), dim3(kBlock), 0,
                            b->stream, reinterpret_cast<const __half*>(L.mem.buf[sl]),
                            reinterpret_cast<double*>(L.mem.pbuf[0]), n, factor);
     hipError_t e = hipGetLastError();

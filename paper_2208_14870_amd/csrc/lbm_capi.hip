@@ -927,11 +927,11 @@ int promote_solver(lbm_solver* s) {
     const long long n = 8 * L.plane;
     const double factor = (L.prec == LBM_FP16) ? std::ldexp(1.0, L.e_scale) : 1.0;
     if (L.prec == LBM_FP32)
-        hipLaunchKernelGGL((k_recast<float, double>), dim3(blocks_for(n)), dim3(kBlock), 0,
+        hipLaunchKernelGGL((k_recast<float, double>), dim3(stride_blocks_for(n)), dim3(kBlock), 0,
                            s->stream, reinterpret_cast<const float*>(L.mem.buf[sl]),
                            reinterpret_cast<double*>(L.mem.pbuf[0]), n, factor);
     else
-        hipLaunchKernelGGL((k_recast<__half, double>), dim3(blocks_for(n)), dim3(kBlock), 0,
+        hipLaunchKernelGGL((k_recast<__half, double>), dim3(stride_blocks_for(n)), dim3(kBlock), 0,
                            s->stream, reinterpret_cast<const __half*>(L.mem.buf[sl]),
                            reinterpret_cast<double*>(L.mem.pbuf[0]), n, factor);
     hipError_t e = hipGetLastError();
@@ -984,7 +984,7 @@ int set_half_exponent(lbm_solver* s, int e_new) {
     if (s->user_state || s->steps > 0) {
         __half* p = reinterpret_cast<__half*>(L.mem.buf[s->sel()]);
         const long long n = 8 * L.plane;
-        hipLaunchKernelGGL((k_recast<__half, __half>), dim3(blocks_for(n)), dim3(kBlock), 0,
+        hipLaunchKernelGGL((k_recast<__half, __half>), dim3(stride_blocks_for(n)), dim3(kBlock), 0,
                            s->stream, p, p, n, std::ldexp(1.0, L.e_scale - e_new));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return s->hip_fail(e, "half rescale");
@@ -1015,7 +1015,7 @@ int rescale_half(lbm_solver* s, double fmax_stored) {
     const int sl = s->sel();
     const long long n = 8 * L.plane;
     __half* p = reinterpret_cast<__half*>(L.mem.buf[sl]);
-    hipLaunchKernelGGL((k_recast<__half, __half>), dim3(blocks_for(n)), dim3(kBlock), 0, s->stream,
+    hipLaunchKernelGGL((k_recast<__half, __half>), dim3(stride_blocks_for(n)), dim3(kBlock), 0, s->stream,
                        p, p, n, std::ldexp(1.0, -k));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return s->hip_fail(e, "rescale");

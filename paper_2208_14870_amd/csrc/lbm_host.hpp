@@ -24,7 +24,13 @@ using namespace lbm;
 // 76 GLUPS).
 constexpr int kItemBand = 8;
 
+// A launch holds fewer than 2^32 threads, and a larger one runs short without an
+// error: a thread per element covers lattices' sites (at most 2^31); passes over
+// whole buffers (eight planes) run stride_blocks_for and walk the rest.
 inline unsigned blocks_for(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+inline unsigned stride_blocks_for(long long n) {
+    return (unsigned)std::min((n + kBlock - 1) / kBlock, 1LL << 23);
+}
 
 constexpr int kErrBlocks = 1024;  // grid of the two-stage FP64 reductions
 
@@ -780,7 +786,7 @@ inline hipError_t launch_stream_only(unsigned grid, hipStream_t st, const StepLa
 inline hipError_t zero_bytes(void* p, size_t bytes, hipStream_t st) {
     const long long words = (long long)(bytes / 4);
     if (words == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero, dim3(blocks_for(words)), dim3(kBlock), 0, st,
+    hipLaunchKernelGGL(k_zero, dim3(stride_blocks_for(words)), dim3(kBlock), 0, st,
                        reinterpret_cast<unsigned int*>(p), words);
     return hipGetLastError();
 }

@@ -116,16 +116,17 @@ static __global__ __launch_bounds__(kBlock) void k_convert(const double* in, C* 
 template <typename SI, typename SO>
 static __global__ __launch_bounds__(kBlock) void k_recast(const SI* in, SO* out, long long n,
                                                    double factor) {
-    const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    double v = (double)Store<SI>::ld(in + i) * factor;
-    Store<SO>::st(out + i, (typename Store<SO>::C)v);
+    const long long step = (long long)gridDim.x * kBlock;
+    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += step) {
+        double v = (double)Store<SI>::ld(in + i) * factor;
+        Store<SO>::st(out + i, (typename Store<SO>::C)v);
+    }
 }
 
 // Zero fill by a kernel (safe inside captured graphs).
 static __global__ __launch_bounds__(kBlock) void k_zero(unsigned int* p, long long nwords) {
-    const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (i < nwords) p[i] = 0u;
+    const long long step = (long long)gridDim.x * kBlock;
+    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < nwords; i += step) p[i] = 0u;
 }
 
 // Deterministic (fixed-order) block reduction of four values; MAXMASK bit c
