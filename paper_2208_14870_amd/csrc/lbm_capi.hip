@@ -121,9 +121,14 @@ struct lbm_solver {
     // The launches of plain steps.  Left to the library, large lattices and all
     // lattices with free rates run through the wavefront at its own depth and
     // segment height; a depth, kernel or height that the caller chose is taken
-    // as given.
+    // as given (higher only where a launch would hold too many threads).
     void make_plan() {
         plan = PlainPlan();
+        choose_plan();
+        if (plan.wave)
+            plan.hs = std::max(plan.hs, wave_least_rows(L.prec, plan.ns, plan.v, L.nx, L.ny));
+    }
+    void choose_plan() {
         const int prec = L.prec;
         if (L.inplace) {
             if (!L.ip_blocked()) return;
@@ -165,6 +170,7 @@ struct lbm_solver {
             plan.ns = sq;
             return;
         }
+        if (!L.wave_fits()) return;
         plan.wave = true;
         plan.ns = depth_auto && fused_auto ? wave_depth(prec) : L.tb;
         plan.v = depth_auto && fused_auto && !gen ? wave_cols_deep(prec, L.nx, L.ny)
@@ -308,9 +314,12 @@ struct lbm_solver {
     // (6 us and more) than the host takes to enqueue it (2.5 us), and a captured
     // graph of them starts 5 us late (solve of 240 x 200 with a check every 100
     // steps, us per step: FP64 1.26 from graphs, 1.18 direct; FP32 1.01, 0.93).
-    // Single steps, which are shorter, replay captured graphs of kGraphSteps.
+    // Single steps, which are shorter, replay captured graphs of kGraphSteps
+    // (a launch of more than 2^30 threads is refused in a graph).
     static constexpr long long kGraphSteps = 64;
-    bool blocked() const { return plan.wave || plan.square || L.fused(); }
+    bool direct() const {
+        return plan.wave || plan.square || L.fused() || (long long)grid * kBlock > (1LL << 30);
+    }
 
     // Launches of np plain steps (two buffers), see next_span.
     long long plain_launches(long long np) const {
@@ -407,7 +416,7 @@ struct lbm_solver {
     // Enqueue a chunk (see kGraphSteps).
     hipError_t enqueue_chunk(long long nplain, bool writeu, bool check) {
         hipError_t e;
-        if (!blocked()) {
+        if (!direct()) {
             for (; nplain >= kGraphSteps; nplain -= kGraphSteps)
                 if ((e = run_graph(kGraphSteps, false, false)) != hipSuccess) return e;
             if (launches(nplain, writeu, check) >= 4) return run_graph(nplain, writeu, check);

@@ -663,9 +663,15 @@ struct Lattice {
     // The tile kernel addresses a plane (populations, and the force in the
     // arithmetic type, which is at least as wide) with 32-bit byte offsets.
     bool tile_fits() const { return plane * (long long)arith_bytes(prec) <= 0xFFFFFFFFLL; }
-    bool fused() const { return tb >= 2 && !general() && !inplace && (wave_hs > 0 || tile_fits()); }
+    // The wavefront addresses a row with them; wider rows run one step per launch.
+    bool wave_fits() const { return wave_row_ok(prec, nx); }
+    bool fused() const {
+        return tb >= 2 && !general() && !inplace && (wave_hs > 0 ? wave_fits() : tile_fits());
+    }
     // in place, up to tb steps per launch through the in-place wavefront
-    bool ip_blocked() const { return inplace && tb >= 2 && !general() && wave_hs > 0; }
+    bool ip_blocked() const {
+        return inplace && tb >= 2 && !general() && wave_hs > 0 && wave_fits();
+    }
     int eff_bxl() const { return fused() ? 6 : bx_log2; }
     int eff_vy() const { return fused() ? th / 4 : (general() ? 1 : vy); }
     int tile_h() const { return (kBlock >> eff_bxl()) * eff_vy(); }

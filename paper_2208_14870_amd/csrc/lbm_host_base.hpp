@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 
 #include "lbm.h"
@@ -37,6 +38,21 @@ hipError_t launch_wave_general(int prec, int ns, int v, unsigned grid, hipStream
 inline bool wave_depth_ok(int prec, int ns) {
     return (ns >= 2 && ns <= 8) || (ns == 12 && prec != LBM_FP16);
 }
+// Rows that the wavefront takes: offsets within a row are 32 bits (the force's
+// elements, of the arithmetic type, are the wider ones), and a launch of one
+// segment (a strip's workgroup of up to 512 threads per 98 columns) holds fewer
+// than 2^32 threads.
+inline bool wave_row_ok(int prec, int nx) {
+    return nx <= (1 << 29) && (long long)nx * (long long)arith_bytes(prec) <= (1LL << 32);
+}
+// The least segment height with fewer than 2^32 threads in a launch.
+inline int wave_least_rows(int prec, int ns, int v, int nx, int ny) {
+    const bool half = prec == LBM_FP16;
+    const int w = wave_out(ns, v, half);
+    const long long strips = ((long long)nx + w - 1) / w;
+    const long long segs = 0xFFFFFFFFLL / (strips * wave_threads(ns, v, half));
+    return (int)((ny + segs - 1) / std::max(1LL, segs));
+}
 // workgroups of that launch that one compute unit holds at a time
 int wave_blocks_per_cu(int prec, int ns, int v);
 
@@ -50,8 +66,8 @@ inline bool is_half(int prec) { return prec == LBM_FP16; }
 constexpr int kSquareSide = 32;
 inline int square_tile(int ns) { return kSquareSide - 2 * (ns - 1); }
 inline long long square_tiles(int ns, int nx, int ny) {
-    const int t = square_tile(ns);
-    return (long long)((nx + t - 1) / t) * ((ny + t - 1) / t);
+    const long long t = square_tile(ns);
+    return ((nx + t - 1) / t) * ((ny + t - 1) / t);
 }
 hipError_t launch_square(int prec, int ns, int nx, int ny, const SlotDesc* slots, int flip,
                          double* partial, bool check, hipStream_t st, bool sr, bool gen);

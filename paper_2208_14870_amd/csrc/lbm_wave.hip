@@ -34,8 +34,9 @@ int wave_blocks_per_cu(int prec, int ns, int v) {
 
 hipError_t launch_wave(int prec, int ns, int v, int nx, int ny, int hs, const SlotDesc* slots,
                        int flip, hipStream_t st, bool sr, bool gen) {
-    if (!wave_depth_ok(prec, ns) || hs < 1 || (v == 2 && (prec == LBM_FP64 || nx % 2 != 0)) ||
-        (v == 2 && prec == LBM_FP16 && ns > 4) || (sr && prec != LBM_FP16) || (sr && gen))
+    if (!wave_depth_ok(prec, ns) || !wave_row_ok(prec, nx) || hs < 1 ||
+        (v == 2 && (prec == LBM_FP64 || nx % 2 != 0)) || (v == 2 && prec == LBM_FP16 && ns > 4) ||
+        (sr && prec != LBM_FP16) || (sr && gen))
         return hipErrorInvalidValue;
     const int w = wave_out(ns, v, is_half(prec));
     WaveLaunch W;

@@ -22,8 +22,8 @@ void launch_halo_t(const WaveLaunch& W, int w, int r, int ns, long long elems, h
 
 hipError_t launch_wave_inplace(int prec, int ns, int v, int nx, int ny, int hs,
                                const SlotDesc* slots, int flip, void* halo, hipStream_t st) {
-    if (!wave_depth_ok(prec, ns) || hs < 1 || !halo || (v == 2 && (prec == LBM_FP64 || nx % 2 != 0)) ||
-        (v == 2 && prec == LBM_FP16 && ns > 4))
+    if (!wave_depth_ok(prec, ns) || !wave_row_ok(prec, nx) || hs < 1 || !halo ||
+        (v == 2 && (prec == LBM_FP64 || nx % 2 != 0)) || (v == 2 && prec == LBM_FP16 && ns > 4))
         return hipErrorInvalidValue;
     const int w = wave_out(ns, v, is_half(prec)), r = wave_ring_of(ns, v);
     WaveLaunch W;
