@@ -118,6 +118,20 @@ struct lbm_solver {
         graphs.clear();
     }
 
+    // The nominal shape of the current storage type, nothing chosen by the caller
+    // (two buffers).
+    void default_shape() {
+        default_tile(L.prec, L.nx, L.ny, L.bx_log2, L.vy);
+        L.tb = default_time_blocking(L.prec, L.N);
+        L.th_user = 0;
+        L.th = fused_th(L.prec, L.tb, L.N);
+        // planes beyond the tile kernel's 32-bit offsets: the wavefront, any width
+        const FusedChoice fc = default_fused(L.prec, L.tb, L.nx, L.ny, cus, !L.tile_fits());
+        L.wave_hs = fc.wave_hs;
+        L.wave_v = fc.wave_v;
+        fused_auto = depth_auto = true;
+    }
+
     // The launches of plain steps.  Left to the library, large lattices and all
     // lattices with free rates run through the wavefront at its own depth and
     // segment height; a depth, kernel or height that the caller chose is taken
@@ -534,14 +548,12 @@ static int create_solver(int nx, int ny, int precision, int with_polish, bool in
     L.prec0 = L.prec = precision;
     L.polish = with_polish != 0 && precision != LBM_FP64 && !inplace;
     L.inplace = inplace;
-    default_tile(precision, nx, ny, L.bx_log2, L.vy);
-    L.tb = inplace ? 1 : default_time_blocking(precision, (long long)nx * ny);
-    L.th = fused_th(precision, L.tb, (long long)nx * ny);
-    // planes beyond the tile kernel's 32-bit offsets: the wavefront, any width
-    const FusedChoice fc = default_fused(precision, L.tb, nx, ny, s->cus, !L.tile_fits());
-    L.wave_hs = inplace ? 0 : fc.wave_hs;
-    L.wave_v = fc.wave_v;
+    s->default_shape();
     if (inplace) {
+        L.tb = 1;
+        L.th = fused_th(precision, 1, L.N);
+        L.wave_hs = 0;
+        L.wave_v = 1;
         // room beyond the minimum holds the in-place wavefront's halo copies:
         // the deepest launch whose default shape fits is the default
         L.halo = reinterpret_cast<char*>(workspace) + need;
@@ -615,7 +627,10 @@ int refit_half(lbm_solver* s);
 int lbm_reset(lbm_solver* s) {
     if (!s) return LBM_E_ARG;
     Lattice& L = s->L;
-    L.prec = L.prec0;
+    if (L.prec != L.prec0) {  // back from FP64: the shape as created
+        L.prec = L.prec0;
+        s->default_shape();
+    }
     L.cur = 0;
     s->phase = 0;
     s->steps = 0;
@@ -948,15 +963,7 @@ int promote_solver(lbm_solver* s) {
     L.prec = LBM_FP64;
     L.cur = 0;
     s->phase = 0;
-    default_tile(LBM_FP64, L.nx, L.ny, L.bx_log2, L.vy);
-    L.tb = default_time_blocking(LBM_FP64, L.N);
-    L.th = fused_th(LBM_FP64, L.tb, L.N);
-    L.th_user = 0;
-    s->depth_auto = true;
-    const FusedChoice fc = default_fused(LBM_FP64, L.tb, L.nx, L.ny, s->cus, !L.tile_fits());
-    L.wave_hs = fc.wave_hs;
-    L.wave_v = fc.wave_v;
-    s->fused_auto = true;
+    s->default_shape();
     // sync_desc folds phase into cur: phase is 0 so cur stays 0
     int rc = s->sync_desc();
     if (rc != LBM_OK) return rc;
