@@ -146,31 +146,9 @@ struct lbm_solver {
         const int prec = L.prec;
         if (L.inplace) {
             if (!L.ip_blocked()) return;
-            plan.wave = true;
-            plan.ns = L.tb;
-            plan.v = L.wave_v;
-            plan.hs = L.wave_hs;
-            if (!fused_auto) return;
-            // the nominal height or longer (fewer row copies; the room for the
-            // halo copies is that of the nominal height), and twelve steps where
-            // longer segments leave the room (FP32 4096 x 3000 2558 us for 64
-            // steps at eight, 2330 at twelve)
-            auto rows = [&](int ns) {
-                const int w = wave_out(ns, plan.v, is_half(prec));
-                const long long strips = (L.nx + w - 1) / w;
-                return wave_segment_rows(ns, cus, wave_blocks_per_cu(prec, ns, plan.v), L.wave_hs,
-                                         L.ny,
-                                         [&](int hs) { return strips * ((L.ny + hs - 1) / hs); });
-            };
-            plan.hs = rows(L.tb);
-            const int deep = wave_depth(prec);
-            if (depth_auto && L.tb == 8 && deep > 8) {
-                const int hs = rows(deep);
-                if (wave_halo_used(prec, deep, plan.v, L.nx, L.ny, hs) <= L.halo_cap) {
-                    plan.ns = deep;
-                    plan.hs = hs;
-                }
-            }
+            plan = inplace_plan(prec, L.nx, L.ny, L.tb, L.wave_v, L.wave_hs, fused_auto, depth_auto,
+                                L.halo_cap, cus,
+                                [&](int ns) { return wave_blocks_per_cu(prec, ns, L.wave_v); });
             return;
         }
         const bool gen = L.general();
@@ -298,8 +276,7 @@ struct lbm_solver {
         hipError_t e = hipSuccess;
         for (long long i = 0; i < np && e == hipSuccess;) {
             const bool nat = L.layout(L.cur ^ (int)(ph & 1)) == kLayNatural;
-            int ns = np - i >= plan.ns ? plan.ns : (int)std::min<long long>(8, np - i);
-            if ((ns & 1) != (nat ? 1 : 0)) ns = ns > 8 ? 7 : ns - 1;
+            const int ns = inplace_span(plan.ns, np - i, nat);
             if (ns >= 2) {
                 e = enqueue_fused_ip(ns, st, ph);
                 i += ns;

@@ -482,6 +482,46 @@ inline int square_depth(int nx, int ny, int cus) {
     return 0;
 }
 inline int wave_depth(int prec) { return prec == LBM_FP16 ? 8 : 12; }
+// Plain steps in place: tb steps per launch over segments of hs rows, v columns
+// per lane.  A height that the library picked (auto_rows) gives way to a longer
+// one (fewer row copies), and eight steps that it picked (auto_depth) to twelve
+// where the longer segments leave the room, which is that of the nominal height
+// (FP32 4096 x 3000 2558 us for 64 steps at eight, 2330 at twelve).  per_cu(ns):
+// workgroups that a compute unit holds.
+template <typename F>
+inline PlainPlan inplace_plan(int prec, int nx, int ny, int tb, int v, int hs, bool auto_rows,
+                              bool auto_depth, size_t room, int cus, F&& per_cu) {
+    PlainPlan p;
+    p.wave = true;
+    p.ns = tb;
+    p.v = v;
+    p.hs = hs;
+    if (!auto_rows) return p;
+    auto rows = [&](int ns) {
+        const int w = wave_out(ns, v, is_half(prec));
+        const long long strips = ((long long)nx + w - 1) / w;
+        return wave_segment_rows(ns, cus, per_cu(ns), hs, ny,
+                                 [&](int h) { return strips * ((ny + h - 1) / h); });
+    };
+    p.hs = rows(tb);
+    const int deep = wave_depth(prec);
+    if (auto_depth && tb == 8 && deep > 8) {
+        const int h = rows(deep);
+        if (wave_halo_used(prec, deep, v, nx, ny, h) <= room) {
+            p.ns = deep;
+            p.hs = h;
+        }
+    }
+    return p;
+}
+// Steps of the next launch in place when `rem` are left, at most `ns` of them, with
+// the parity that the layout needs (0: a single step).
+inline int inplace_span(int ns, long long rem, bool natural) {
+    const int k = rem >= ns ? ns : (int)std::min<long long>(8, rem);
+    if ((k & 1) == (natural ? 1 : 0)) return k;
+    return k > 8 ? 7 : k - 1;
+}
+
 // Columns per lane of the wavefront at that depth: two for FP32 on even widths
 // from 12 M sites, where the lattice no longer fits the caches and fewer loads
 // per site (two columns in one access, ring of 24 per 104 columns instead of per
