@@ -234,19 +234,11 @@ def make_solvers(cases, prec, kernel="default"):
     return out
 
 
-def plain_depth(cfg, ctype, chosen=False):
-    """Steps per launch of plain steps: the launch config's when the caller
-    chose it, else the library's own depth where the wavefront is the default
-    (twelve for FP64 and FP32)."""
-    if chosen or cfg["kernel"] != "wavefront" or ctype == "__half":
-        return cfg["steps_per_launch"]
-    return 12
-
-
-def kernel_label(cfg, ctype, sites, sr=False, chosen=False):
+def kernel_label(cfg, ctype, sites, sr=False):
     """Name (with its full template arguments, as the profiler names it) and
-    algorithmic traffic of the plain-step kernel of a launch config."""
-    tb, rows, nt = plain_depth(cfg, ctype, chosen), cfg["rows"], cfg["threads"]
+    algorithmic traffic of the kernel that plain steps run through (a
+    Solver.plain_launch record)."""
+    tb, rows, nt = cfg["steps_per_launch"], cfg["rows"], cfg["threads"]
     per_site = {"double": 144, "float": 72, "__half": 40}[ctype]
     side = int(round(math.sqrt(sites)))
     srs = "true" if sr else "false"
@@ -259,6 +251,10 @@ def kernel_label(cfg, ctype, sites, sr=False, chosen=False):
         return (f"k_wave<{ctype}, {tb}, {v}, {srs}, false, false, false> (wavefront over the waves "
                 f"of a workgroup): {tb} fused steps per launch, "
                 f"{per_site} B per site-update algorithmic, {tb} x {side}^2 site-updates per launch")
+    if cfg["kernel"] == "square":
+        return (f"k_stepS<{ctype}, {tb}, 0, {srs}, false> (32 x 32 regions, {nt} threads): {tb} "
+                f"fused steps per launch, {per_site} B per site-update algorithmic, "
+                f"{tb} x {side}^2 site-updates per launch")
     return f"k_step<{ctype}, ...>: one step per launch, {per_site} B per site-update algorithmic"
 
 
@@ -272,8 +268,8 @@ def run_workload(solvers, nchunks, chunk):
     ev = []
     last = []
     history = []  # residual of the first case after every chunk
-    first = solvers[0][0]
-    tb = min(plain_depth(first.launch_config(), ""), max(2, chunk // 2))
+    cfg = solvers[0][0].plain_launch()
+    tb = min(cfg["steps_per_launch"], max(2, chunk // 2))
     checked = max(2, tb)  # the chunk's last launch carries the residual check
     per = chunk - checked
     fused, rest = per - per % tb, per % tb
@@ -299,7 +295,7 @@ def run_workload(solvers, nchunks, chunk):
     plain_ms = sum(a.elapsed_time(b) for a, b in ev)
     return {"wall_s": wall, "plain_kernel_avg_us": 1e3 * plain_ms / (len(ev) * (fused // tb)),
             "plain_us_per_step": 1e3 * plain_ms / (len(ev) * fused),
-            "steps_per_launch": tb, "launch_config": solvers[0][0].launch_config(),
+            "steps_per_launch": tb, "launch_config": cfg,
             "last": last[-len(solvers):], "history": history}
 
 
@@ -443,19 +439,19 @@ def large_lattice(steps=10000, warm=200, precs=("fp64", "fp32", "fp16", "fp16sr"
         e1.record()
         torch.cuda.synchronize()
         us = 1e3 * e0.elapsed_time(e1) / steps  # per step
-        cfg = s.launch_config()
+        cfg = s.plain_launch()
         ux, uy = s.displacement()
         u[key] = (ux[::32, ::32].clone(), uy[::32, ::32].clone())
         del ux, uy
         s.close()
         del s
         ctype = {"fp64": "double", "fp32": "float", "fp16": "__half"}[prec]
-        tbl = plain_depth(cfg, ctype, bool(tb))
+        tbl = cfg["steps_per_launch"]
         launches = steps // tbl + (1 if steps % tbl else 0)
         out[key] = {"mlups": round(sites / us, 1), "us_per_step": round(us, 2),
                     "launch_config": cfg,
                     "roofline": roofline(prec, sites, us * steps / launches, tbl,
-                                         kernel_label(cfg, ctype, sites, key == "fp16sr", bool(tb)),
+                                         kernel_label(cfg, ctype, sites, key == "fp16sr"),
                                          (f"k_stepN_{prec}_8192_counters" if cfg["kernel"] == "tile"
                                           else f"k_wave_{prec}_8192_counters")
                                          if key == prec else None)}
@@ -505,7 +501,7 @@ def inplace_run(n=8192, steps=400, warm=8):
             torch.cuda.synchronize()
             us = 1e3 * e0.elapsed_time(e1) / steps
             r = {"mlups": round(n * n / us, 1), "workspace_bytes": s.workspace_bytes,
-                 "launch_config": s.launch_config()}
+                 "launch_config": s.plain_launch()}
             if tb == 1:
                 gbs = BYTES_PER_SITE[prec] * n * n / (us * 1e-6) / 1e9
                 r.update(gbs=round(gbs, 1), frac=round(gbs / PEAK_HBM_GBS, 4))

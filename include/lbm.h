@@ -418,18 +418,30 @@ int lbm_set_fused_kernel(lbm_solver *s, int kind, int segment_rows);
  * or in place). */
 int lbm_set_stochastic_rounding(lbm_solver *s, int on, unsigned int seed);
 
-/* Current launch configuration of plain steps: out[0] steps per launch;
+/* Nominal launch configuration of plain steps: out[0] steps per launch;
  * out[1] the fused kernel (LBM_FUSED_TILE, LBM_FUSED_WAVEFRONT, or -1 for one
  * step per launch); out[2] its tile rows (tile), segment rows (wavefront) or
  * rows per thread (one step per launch); out[3] threads per workgroup (of the
- * wavefront: 256, four waves).  This is the shape that the lbm_set_* calls
- * start from and change; while none has been called, the wavefront runs at the
- * library's own depth and segment height instead (lbm_set_time_blocking), with
- * the threads its depth needs.
- * out is a host array of 4 ints.  Errors: LBM_E_ARG. */
+ * wavefront: 256).  This is the shape that the lbm_set_* calls start from and
+ * change; while none has been called, another may run
+ * (lbm_get_plain_launch).  out is a host array of 4 ints.  Errors: LBM_E_ARG. */
 int lbm_get_launch_config(const lbm_solver *s, int out[4]);
 
-/* Columns per lane of the wavefront when the current launch configuration has
+/* The small-lattice kernel, in lbm_get_plain_launch only: square regions of
+ * 32 x 32 sites, one per thread, whose tiles are no more than the compute
+ * units. */
+enum { LBM_FUSED_SQUARE = 2 };
+
+/* What plain steps run through at present: out[0] steps of a full launch;
+ * out[1] the kernel (LBM_FUSED_TILE, LBM_FUSED_WAVEFRONT, LBM_FUSED_SQUARE, or
+ * -1 for one step per launch); out[2] its tile rows (tile), segment rows
+ * (wavefront), the side of its tiles (square) or rows per thread (one step per
+ * launch); out[3] threads per workgroup; out[4] columns per lane (wavefront,
+ * else 0).  A remainder of a sequence of steps runs shallower launches.  out is a
+ * host array of 5 ints.  Errors: LBM_E_ARG. */
+int lbm_get_plain_launch(const lbm_solver *s, int out[5]);
+
+/* Columns per lane of the wavefront when the nominal launch configuration has
  * it (1 or 2), 0 otherwise.  Errors: LBM_E_ARG. */
 int lbm_get_wave_columns(const lbm_solver *s);
 

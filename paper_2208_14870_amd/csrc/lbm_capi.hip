@@ -893,6 +893,36 @@ int lbm_get_launch_config(const lbm_solver* s, int out[4]) {
     return LBM_OK;
 }
 
+int lbm_get_plain_launch(const lbm_solver* s, int out[5]) {
+    if (!s || !out) return LBM_E_ARG;
+    const Lattice& L = s->L;
+    const PlainPlan& p = s->plan;
+    out[4] = 0;
+    if (p.square) {
+        out[0] = p.ns;
+        out[1] = LBM_FUSED_SQUARE;
+        out[2] = square_tile(p.ns);
+        out[3] = kSquareSide * kSquareSide;
+    } else if (p.wave) {
+        out[0] = p.ns;
+        out[1] = LBM_FUSED_WAVEFRONT;
+        out[2] = p.hs;
+        out[3] = wave_threads(p.ns, p.v, is_half(L.prec));
+        out[4] = p.v;
+    } else if (L.fused()) {
+        out[0] = L.tb;
+        out[1] = LBM_FUSED_TILE;
+        out[2] = L.th;
+        out[3] = fused_nt(L.prec, L.tb, L.th);
+    } else {
+        out[0] = 1;
+        out[1] = -1;
+        out[2] = L.inplace ? 0 : L.eff_vy();
+        out[3] = kBlock;
+    }
+    return LBM_OK;
+}
+
 int lbm_get_wave_columns(const lbm_solver* s) {
     if (!s) return LBM_E_ARG;
     return ((s->L.fused() && s->L.wave_hs > 0) || s->L.ip_blocked()) ? s->L.wave_v : 0;

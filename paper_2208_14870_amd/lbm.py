@@ -84,6 +84,7 @@ def load() -> ctypes.CDLL:
         "lbm_set_stochastic_rounding": (i, [vp, i, ctypes.c_uint]),
         "lbm_set_tile_rows": (i, [vp, i]),
         "lbm_get_launch_config": (i, [vp, pi]),
+        "lbm_get_plain_launch": (i, [vp, pi]),
         "lbm_get_wave_columns": (i, [vp]),
         "lbm_workspace_bytes_inplace": (sz, [i, i, i]),
         "lbm_workspace_bytes_inplace_blocked": (sz, [i, i, i, i, i]),
@@ -349,10 +350,23 @@ class Solver:
     def set_time_blocking(self, steps_per_launch: int):
         self._check(self.lib.lbm_set_time_blocking(self.h, int(steps_per_launch)))
 
+    def plain_launch(self) -> dict:
+        """What plain steps run through at present: steps of a full launch, kernel
+        ("tile", "wavefront", "square" or "single"), its rows, threads per
+        workgroup and columns per lane; see lbm_get_plain_launch."""
+        out = (ctypes.c_int * 5)()
+        self._check(self.lib.lbm_get_plain_launch(self.h, out))
+        kind = {0: "tile", 1: "wavefront", 2: "square"}.get(out[1], "single")
+        cfg = {"steps_per_launch": out[0], "kernel": kind, "rows": out[2], "threads": out[3]}
+        if kind == "wavefront":
+            cfg["columns_per_lane"] = out[4]
+        return cfg
+
     def launch_config(self) -> dict:
-        """Steps per launch, fused kernel ("tile", "wavefront" or "single"),
-        its rows (tile rows, segment rows, or rows per thread) and threads per
-        workgroup; see lbm_get_launch_config."""
+        """The nominal shape, which the set_* calls start from (what runs:
+        plain_launch): steps per launch, fused kernel ("tile", "wavefront" or
+        "single"), its rows (tile rows, segment rows, or rows per thread) and
+        threads per workgroup; see lbm_get_launch_config."""
         out = (ctypes.c_int * 4)()
         self._check(self.lib.lbm_get_launch_config(self.h, out))
         kind = {0: "tile", 1: "wavefront"}.get(out[1], "single")
