@@ -1,0 +1,92 @@
+"""Wavefront launches that only some options reach (free relaxation rates, in
+place at twelve steps, the default rule's smallest lattices), against single
+steps bit for bit: every level is rounded as a store would round it, so no
+tolerance.  Each case asserts that the wavefront is what runs."""
+import numpy as np
+import pytest
+
+from gpu_common import dev, host, need_gpu, say
+from paper_2208_14870_amd import problem as P
+
+pytestmark = pytest.mark.gpu
+
+RATES = (0.3, 0.93, 0.9, 1.12)
+
+
+def _states(nx, ny, prec, steps, shape=None, want=None, rates=None, sr=False, inplace=False):
+    """Populations after each of `steps` (cumulative); shape(solver) sets the
+    launch shape, want: (depth, columns per lane) of the wavefront."""
+    from paper_2208_14870_amd import lbm
+    need_gpu()
+    rng = np.random.default_rng(nx * 31 + ny)
+    f0 = rng.standard_normal((8, ny, nx))
+    g = rng.standard_normal((2, ny, nx)) * 1e-2
+    g -= g.mean(axis=(1, 2), keepdims=True)
+    mat = P.Material.from_shear_poisson(0.9, 0.3)
+    s = lbm.Solver(nx, ny, prec, inplace=inplace)
+    if rates:
+        s.set_rates(*rates)
+    s.set_material(mat.lame_lambda, mat.lame_mu)
+    if sr:
+        s.set_stochastic_rounding(True, 7)
+    s.set_body_force(dev(g[0]), dev(g[1]))
+    s.set_populations(dev(f0))
+    if shape:
+        shape(s)
+    if want:
+        p = s.plain_launch()
+        assert p["kernel"] == "wavefront", p
+        assert (p["steps_per_launch"], p["columns_per_lane"]) == want, p
+    out = []
+    for n in steps:
+        s.step(n)
+        out.append(host(s.populations()))
+    s.close()
+    return out
+
+
+def _same(nx, ny, prec, steps, shape=None, want=None, **kw):
+    say(f"wavefront {prec} {nx}x{ny} {want} {kw}")
+    got = _states(nx, ny, prec, steps, shape, want, **kw)
+    kw.pop("inplace", None)
+    ref = _states(nx, ny, prec, steps, lambda s: s.set_time_blocking(1), **kw)
+    for n, a, b in zip(np.cumsum(steps), got, ref):
+        np.testing.assert_array_equal(a, b, err_msg=f"after {n} steps")
+
+
+# below one strip, at and one beyond a strip's output columns (wide and narrow),
+# odd and even, short and tall; segments shorter and longer than the lattice
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("nx,ny,rows", [(1, 1, 4), (3, 2, 1), (20, 21, 7), (97, 31, 16), (106, 12, 5),
+                                        (109, 50, 64), (250, 13, 13), (122, 40, 9)])
+def test_general_rates_through_the_chosen_wavefront(prec, nx, ny, rows):
+    """Free relaxation rates at every chosen depth: full launches and every
+    remainder."""
+    for depth in range(2, 9):
+        v = 2 if prec != "fp64" and nx % 2 == 0 and depth <= 4 else 1
+
+        def shape(s):
+            s.set_time_blocking(depth)
+            s.set_fused_kernel("wavefront", rows)
+        _same(nx, ny, prec, (depth, 2 * depth + depth // 2, 3), shape, (depth, v), rates=RATES)
+
+
+# just past the small-lattice rule: strips of 98 (108 for half storage) columns
+# filled exactly, one beyond, and ragged
+@pytest.mark.parametrize("prec,nx,ny", [("fp64", 490, 420), ("fp64", 491, 419), ("fp32", 490, 420),
+                                        ("fp32", 491, 419), ("fp16", 540, 400), ("fp16", 541, 401)])
+def test_general_rates_at_the_default_depth(prec, nx, ny):
+    """Free relaxation rates at the library's own depth: full launches, and the
+    remainders of one and of two launches."""
+    deep = 8 if prec == "fp16" else 12
+    _same(nx, ny, prec, (deep, 9, 11, 2 * deep + 10, 7), None, (deep, 1), rates=RATES)
+
+
+# sizes whose longer segments leave the room for twelve steps: odd and even
+# widths, one and two columns per lane, heights that the segments do not divide
+@pytest.mark.parametrize("prec,nx,ny,v", [("fp64", 1000, 1000, 1), ("fp64", 701, 1536, 1),
+                                          ("fp32", 1001, 1000, 1), ("fp32", 2048, 1536, 2)])
+def test_in_place_at_twelve_steps(prec, nx, ny, v):
+    """In place at the default depth, from both layouts, with remainders of every
+    kind."""
+    _same(nx, ny, prec, (13, 12, 23, 24, 35, 1, 12), None, (12, v), inplace=True)
