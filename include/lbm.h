@@ -540,6 +540,12 @@ int lbm_batch_get_displacement(lbm_batch *b, int slot, double *ux, double *uy);
  * 3..8). */
 int lbm_batch_set_tile(lbm_batch *b, int bx_log2, int rows_per_thread, int blocks_per_cu);
 
+/* What plain steps of a storage type run through at present, as
+ * lbm_get_plain_launch (out[1] LBM_FUSED_WAVEFRONT once lattices are on the
+ * wavefront list; out[2] the tile rows of the others and of checks).  Errors:
+ * LBM_E_ARG, LBM_E_HIP. */
+int lbm_batch_get_plain_launch(lbm_batch *b, int precision, int out[5]);
+
 /* Temporal blocking for all lattices of the batch (see lbm_set_time_blocking,
  * 1..8).  Until set, a storage type with lattices on the wavefront list runs
  * eight steps per launch (FP64 and FP32 twelve when all of its lattices are on

@@ -177,7 +177,8 @@ struct lbm_batch {
     // lattices of each storage type with at least this many sites take the
     // wavefront list (-1: the default rule, see on_wave_list)
     long long wave_min[3] = {-1, -1, -1};
-    bool wave_all[3] = {false, false, false};  // default rule, total above batch_wave_total
+    bool wave_all[3] = {false, false, false};  // default rule: the list for every lattice
+    int wave_v[3] = {1, 1, 1};                 // the list's shape (lbm_wave_shape.hpp)
     // fused tile height per precision, from the precision's current total sites
     // (short tiles once few sites remain, e.g. the tail of a set of solves)
     int th[3] = {8, 16, 12};
@@ -267,16 +268,35 @@ struct lbm_batch {
         for (int p = 0; p < 3; ++p) {
             long long sites = 0;
             bool large = false, small = false;  // a lattice on / not on the wavefront list
-            for (int i = 0; i < max_slots; ++i)
-                if (slots[i].active && slots[i].L.prec == p) sites += slots[i].L.N;
-            wave_all[p] = sites >= batch_wave_total(p);
-            for (int i = 0; i < max_slots; ++i)
-                if (slots[i].active && slots[i].L.prec == p)
-                    (on_wave_list(p, slots[i].L.N) ? large : small) = true;
+            double tiles = 0.0;
+            // its lattices on the list (or all of them) through a shape of the wavefront
+            auto total = [&](bool all, int v, int ns) {
+                double t = 0.0;
+                for (const BSlot& s : slots)
+                    if (s.active && s.L.prec == p && (all || on_wave_list(p, s.L.N)))
+                        t += wave_cost(p, v, ns, s.L.nx, s.L.ny);
+                return t;
+            };
+            for (const BSlot& s : slots)
+                if (s.active && s.L.prec == p) {
+                    sites += s.L.N;
+                    tiles += tile_cost(p, s.L.nx, s.L.ny);
+                }
+            wave_all[p] = false;
+            if (sites >= batch_wave_total(p) && wave_min[p] < 0) {
+                int v, ns;
+                wave_best_shape(p, [&](int a, int b) { return total(true, a, b); }, v, ns);
+                wave_all[p] = wave_over_tile(total(true, v, ns), tiles);
+            }
+            for (const BSlot& s : slots)
+                if (s.active && s.L.prec == p) (on_wave_list(p, s.L.N) ? large : small) = true;
             // the wavefront runs its own depth best, and its lattices carry the
             // work; beside lattices on the tile kernel the eight steps that both run
-            if (tb_auto[p])
-                tb[p] = !large ? default_time_blocking(p, sites, true) : small ? 8 : wave_depth(p);
+            auto listed = [&](int v, int ns) { return total(false, v, ns); };
+            wave_v[p] = 1;
+            if (tb_auto[p]) tb[p] = !large ? default_time_blocking(p, sites, true) : 8;
+            if (large && !small && tb_auto[p]) wave_best_shape(p, listed, wave_v[p], tb[p]);
+            else if (large && tb[p] >= 2) wave_v[p] = wave_best_width(tb[p], listed);
             th[p] = fused_th(p, tb[p], sites);
         }
         // Per precision: the tile work list of every lattice (single steps and
@@ -288,7 +308,7 @@ struct lbm_batch {
             range_host[p][0] = (int)total;
             wrange_host[p][0] = (int)h_witems.size();
             int wave_ny = 0;  // rows of its tallest wavefront lattice
-            const int w = tb[p] >= 2 ? wave_out(tb[p], 1, is_half(p)) : 0;
+            const int w = tb[p] >= 2 ? wave_out(tb[p], wave_v[p], is_half(p)) : 0;
             for (int pass = 0; pass < 2; ++pass) {
                 for (int i = 0; i < max_slots; ++i) {
                     BSlot& s = slots[i];
@@ -318,7 +338,7 @@ struct lbm_batch {
                         n += (long long)((s.L.nx + w - 1) / w) * ((s.L.ny + hs - 1) / hs);
                 return n;
             };
-            const int hs = wave_ny ? wave_segment_rows(tb[p], cus, wave_blocks_per_cu(p, tb[p], 1),
+            const int hs = wave_ny ? wave_segment_rows(tb[p], cus, wave_blocks_per_cu(p, tb[p], wave_v[p]),
                                                        16, wave_ny, groups)
                                    : 1;
             // segments of equal height per lattice, the longest first: the last
@@ -456,7 +476,7 @@ struct lbm_batch {
                 hipError_t r = hipSuccess;
                 if (gt) r = launch_stepN(p, ns, th[p], gt, st, args(p, flip, true));
                 if (r == hipSuccess && gw)
-                    r = launch_wave_list(p, ns, d_desc, d_witems, d_wrange + 2 * p, nw, flip, gw, st);
+                    r = launch_wave_list(p, ns, wave_v[p], d_desc, d_witems, d_wrange + 2 * p, nw, flip, gw, st);
                 return r;
             };
             for (; i < np && e == hipSuccess; ++ph) {
@@ -884,6 +904,23 @@ int lbm_batch_get_displacement(lbm_batch* b, int slot, double* ux, double* uy) {
     const BSlot& s = b->slots[slot];
     hipError_t e = extract_u(s.L.prec, s.L.desc(), b->sel(s), kLayPull, ux, uy, b->stream);
     if (e != hipSuccess) return b->hip_fail(e, "batch_get_displacement");
+    return LBM_OK;
+}
+
+int lbm_batch_get_plain_launch(lbm_batch* b, int precision, int out[5]) {
+    if (!b) return LBM_E_ARG;
+    if (!valid_prec(precision) || !out)
+        return b->fail(LBM_E_ARG, "batch_get_plain_launch: precision LBM_FP64/FP32/FP16, NULL output");
+    const int rc = b->ensure();
+    if (rc != LBM_OK) return rc;
+    const int p = precision, tb = b->tb[p];
+    const bool list = b->wrange_host[p][1] > b->wrange_host[p][0];
+    out[0] = tb;
+    out[1] = tb < 2 ? -1 : list ? LBM_FUSED_WAVEFRONT : LBM_FUSED_TILE;
+    out[2] = tb < 2 ? b->vy : b->th[p];
+    out[3] = tb < 2 ? kBlock
+             : list ? wave_threads(tb, b->wave_v[p], is_half(p)) : fused_nt(p, tb, b->th[p]);
+    out[4] = tb >= 2 && list ? wave_lane_cols(b->wave_v[p]) : 0;
     return LBM_OK;
 }
 

@@ -352,17 +352,16 @@ inline bool wave_by_default(int prec, long long n) {
     return (prec == LBM_FP64 && n >= 458752) || (prec == LBM_FP32 && n >= (1LL << 20)) ||
            (prec == LBM_FP16 && n >= (1LL << 24));
 }
-// In a batch, lattices of one storage type fill the chip together, so above
-// these totals every lattice of the type takes the wavefront list (us per step,
-// tile kernel / wavefront list: FP64 16 lattices 48..256 (0.32 M sites) 3.93 /
-// 2.73, 8 of 48..128 (0.09 M) 1.76 / 2.59, 128 of 48..128 (1.1 M) 12.8 / 8.8, 256
-// of 64..512 (18 M) 163 / 72; FP32 32 of 48..128 (0.28 M) 2.39 / 2.41, 16 of
-// 48..256 (0.32 M) 2.51 / 2.25, 128 of 48..128 6.01 / 5.02, 256 of 64..512 62.7 /
-// 41.5; FP16 128 of 48..128 5.20 / 5.19, 64 of 64..256 (1.5 M) 5.98 / 6.16, 32 of
-// 100..512 (2.2 M) 7.75 / 6.86, 256 of 64..512 51.7 / 42.6).  Below them only the
-// lattices of wave_by_default do.
+// In a batch, lattices of one storage type fill the chip together: above these
+// totals every lattice of the type takes the wavefront list where its strips fit
+// the lattices (wave_over_tile).  Below, the few workgroups of a launch are a
+// chain of latencies and the tile kernel's are shorter (us per step, list / tile:
+// FP64 64^2 0.21 M sites 2.44 / 2.07, 0.32 M 2.85 / 3.58, 1 M 6.1 / 9.0; FP32 128^2
+// 0.32 M 2.31 / 2.00, 0.5 M 2.53 / 2.22, 0.8 M 3.34 / 3.49, 2 M 6.6 / 7.6; 256^2
+// 0.5 M 2.29 / 2.23, 0.8 M 2.95 / 3.44; FP16 256^2 1 M 3.87 / 3.50, 2.2 M 6.79 /
+// 6.99; 98^2 2.2 M 6.9 / 10.6).  Only the lattices of wave_by_default do then.
 inline long long batch_wave_total(int prec) {
-    return prec == LBM_FP64 ? 200000 : prec == LBM_FP32 ? 300000 : (1LL << 21);
+    return prec == LBM_FP64 ? 300000 : prec == LBM_FP32 ? 700000 : (1LL << 21);
 }
 struct FusedChoice {
     int wave_hs = 0, wave_v = 1;
@@ -421,6 +420,60 @@ struct PlainPlan {
     bool square = false;  // the small-lattice kernel
     int ns = 0, v = 1, hs = 0;
 };
+
+// Time of a row of a wavefront's workgroup, by shape (v, see lbm_wave_shape.hpp)
+// and steps per launch, against the two-wave shape at the library's depth; from
+// batches of equal lattices of 16^2 to 144^2, 8x1000, 16x400 and 40x200 that fill
+// the chip (FP64 4.4 M sites, FP32 9 M, FP16 17 M).  A strip of one wave takes
+// half as long, a shallower pipeline a little less.
+inline double wave_row_time(int prec, int v, int ns) {
+    const bool deep = ns > 8 || prec == LBM_FP16;
+    if (prec == LBM_FP64) return v == 0 ? (deep ? 0.48 : 0.45) : (deep ? 1.0 : 0.87);
+    if (prec == LBM_FP32) return v == 0 ? (deep ? 0.50 : 0.43) : (deep ? 1.0 : 0.92);
+    return v == 0 ? 0.54 : 1.0;
+}
+// A step of an nx x ny lattice through the wavefront, in such rows (halo rows for
+// segments of up to 512).
+inline double wave_cost(int prec, int v, int ns, int nx, int ny) {
+    const int w = wave_out(ns, v, is_half(prec));
+    const double strips = std::ceil((double)nx / w), segs = std::ceil(ny / 512.0);
+    return strips * (ny + 2.0 * ns * segs) * wave_row_time(prec, v, ns) / ns;
+}
+// The same through the LDS tile kernel at its own depth, from the same batches.
+inline double tile_cost(int prec, int nx, int ny) {
+    const int th = prec == LBM_FP64 ? 8 : 16;
+    const double tiles = std::ceil(nx / 64.0) * std::ceil((double)ny / th);
+    return tiles * (prec == LBM_FP64 ? 1.19 : prec == LBM_FP32 ? 2.09 : 2.06);
+}
+// Whether lattices of these costs run faster through the wavefront.  The costs
+// are those of a full chip; up to 0.86 the wavefront was the faster one at every
+// total above batch_wave_total (FP32 56^2 0.80: 1.01 to 1.09 times as fast; FP32
+// 64^2 0.88: 0.80 to 1.10; FP16 128^2 0.88: 0.94 to 1.12).
+inline bool wave_over_tile(double wave, double tile) { return wave < 0.86 * tile; }
+// Shape and depth of the wavefront that takes the least time for the lattices of
+// total(v, ns): two waves per strip at the library's depth unless another is
+// clearly better.  Strips leave columns idle where they do not divide a width:
+// 32^2 in 98 columns, 100 columns in two strips of 98 (us per step, FP64 batches
+// of 4.4 M sites, two waves at twelve / one wave at twelve / one at eight / two at
+// eight: 32^2 58.9 / 31.5 / 35.9 / 62.8, 48^2 37.1 / 34.4 / 25.8 / 41.9, 100^2
+// 32.5 / 25.9 / 30.7 / 23.7, 128^2 29.3 / 25.1 / 26.3 / 33.2, 98^2 18.8 / 24.8 /
+// 31.3 / 23.5).
+template <typename F>
+inline int wave_best_width(int ns, F&& total) {  // at a given depth
+    return total(0, ns) < 0.97 * total(1, ns) ? 0 : 1;
+}
+template <typename F>
+inline void wave_best_shape(int prec, F&& total, int& v, int& ns) {
+    const int deep = prec == LBM_FP16 ? 8 : 12;
+    v = wave_best_width(deep, total);
+    ns = deep;
+    if (deep == 8) return;
+    const int v8 = wave_best_width(8, total);
+    if (total(v8, 8) < 0.97 * total(v, deep)) {
+        v = v8;
+        ns = 8;
+    }
+}
 
 // Segment rows of a wavefront over `groups(hs)` workgroups, `per_cu` of which a
 // compute unit holds at a time: the height that finishes first.  A workgroup

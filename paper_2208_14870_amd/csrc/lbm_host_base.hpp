@@ -103,7 +103,7 @@ inline size_t wave_halo_bytes(int prec, int ns, int v, int nx, int ny, int hs) {
 // descriptor slot, strip (as wide as the output of the list's depth ns' >= ns:
 // a shallower launch leaves the surplus strips idle) and rows.  nitems: the
 // list's current length, to check the grid.  Defined in lbm_wave_batch.hip.
-hipError_t launch_wave_list(int prec, int ns, const SlotDesc* slots, const WaveItem* items,
+hipError_t launch_wave_list(int prec, int ns, int v, const SlotDesc* slots, const WaveItem* items,
                             const int* wrange, int nitems, int flip, unsigned grid,
                             hipStream_t st);
 

@@ -14,10 +14,14 @@ namespace lbm_host {
 namespace {
 template <typename F>
 void for_wave(int prec, int ns, int v, bool sr, F&& run) {
-    if (prec == LBM_FP64) wave_dispatch<double, 1, false, false, false, false>(ns, run);
+    if (prec == LBM_FP64 && v == 0) wave_dispatch<double, 0, false, false, false, false>(ns, run);
+    else if (prec == LBM_FP64) wave_dispatch<double, 1, false, false, false, false>(ns, run);
     else if (prec == LBM_FP32 && v == 2) wave_dispatch<float, 2, false, false, false, false>(ns, run);
+    else if (prec == LBM_FP32 && v == 0) wave_dispatch<float, 0, false, false, false, false>(ns, run);
     else if (prec == LBM_FP32) wave_dispatch<float, 1, false, false, false, false>(ns, run);
     else if (v == 2 && sr) wave_dispatch<__half, 2, true, false, false, false>(ns, run);
+    else if (v == 0 && sr) wave_dispatch<__half, 0, true, false, false, false>(ns, run);
+    else if (v == 0) wave_dispatch<__half, 0, false, false, false, false>(ns, run);
     else if (sr) wave_dispatch<__half, 1, true, false, false, false>(ns, run);
     else if (v == 2) wave_dispatch<__half, 2, false, false, false, false>(ns, run);
     else wave_dispatch<__half, 1, false, false, false, false>(ns, run);

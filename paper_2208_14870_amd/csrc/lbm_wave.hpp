@@ -103,15 +103,16 @@ template <> struct VecIO<__half, 2> {
     }
 };
 
-template <typename S, int NS, int V>
+template <typename S, int NS, int VS>
 struct WaveShape {
+    static constexpr int V = wave_lane_cols(VS);  // columns per lane
     static constexpr bool kHalf = std::is_same<S, __half>::value;
     static constexpr int LPW = wave_levels(kHalf), LF = wave_min(LPW, NS);
     static constexpr int NG = wave_groups(NS, kHalf);
-    static constexpr int XW = wave_across(V), OVL = wave_overlap(NS, V, kHalf);
-    static constexpr int R = wave_ring_of(NS, V);
-    static constexpr int TC = wave_strip(NS, V, kHalf), W = wave_out(NS, V, kHalf);
-    static constexpr int NT = wave_threads(NS, V, kHalf);
+    static constexpr int XW = wave_across(VS), OVL = wave_overlap(NS, VS, kHalf);
+    static constexpr int R = wave_ring_of(NS, VS);
+    static constexpr int TC = wave_strip(NS, VS, kHalf), W = wave_out(NS, VS, kHalf);
+    static constexpr int NT = wave_threads(NS, VS, kHalf);
     static constexpr int PF = 2;  // rows loaded ahead
     // waves per SIMD to allocate registers for
     static constexpr int WPE = (V == 1 && !std::is_same<S, double>::value) ? 4 : 2;
@@ -236,13 +237,13 @@ __device__ __forceinline__ void wave_barrier() {
 // k_wave_halo), from kLayNatural for odd NS, kLaySwapped for even.  GEN: free
 // relaxation rates.  FIRST / LAST: the group that loads / stores.  Every wave
 // passes `total` barriers, whatever its group and its own first and last row.
-template <typename S, int NS, int V, bool SR, bool IP, bool GEN, bool FIRST, bool LAST>
+template <typename S, int NS, int VS, bool SR, bool IP, bool GEN, bool FIRST, bool LAST>
 __device__ __forceinline__ void wave_group(const WaveLaunch& L, const SlotDesc& d, S* pops,
                                            typename Store<S>::C* force, int grp, int xb, int sx,
                                            int sy, int ya, int yb) {
     using C = typename Store<S>::C;
-    using Sh = WaveShape<S, NS, V>;
-    constexpr int R = Sh::R, W = Sh::W, TC = Sh::TC, NG = Sh::NG, XW = Sh::XW, PF = GEN ? 1 : Sh::PF;
+    using Sh = WaveShape<S, NS, VS>;
+    constexpr int V = Sh::V, R = Sh::R, W = Sh::W, TC = Sh::TC, NG = Sh::NG, XW = Sh::XW, PF = GEN ? 1 : Sh::PF;
     constexpr bool kSR = SR && std::is_same<S, __half>::value;
     constexpr bool kNat = IP && (NS % 2 == 1);      // level 0 is f(n) itself
     constexpr int NL = LAST ? NS - Sh::before(NG - 1) : Sh::LPW;  // levels of this group
@@ -501,12 +502,12 @@ __device__ __forceinline__ void wave_group(const WaveLaunch& L, const SlotDesc& 
 
 // LIST: each workgroup takes its lattice, strip and rows from L.items (a batch
 // of lattices; two buffers, no stochastic rounding).
-template <typename S, int NS, int V, bool SR = false, bool IP = false, bool LIST = false,
+template <typename S, int NS, int VS, bool SR = false, bool IP = false, bool LIST = false,
           bool GEN = false>
-static __global__ __launch_bounds__((WaveShape<S, NS, V>::NT))
-__attribute__((amdgpu_waves_per_eu(WaveShape<S, NS, V>::WPE - (GEN && WaveShape<S, NS, V>::WPE > 2)))) void k_wave(WaveLaunch L) {
+static __global__ __launch_bounds__((WaveShape<S, NS, VS>::NT))
+__attribute__((amdgpu_waves_per_eu(WaveShape<S, NS, VS>::WPE - (GEN && WaveShape<S, NS, VS>::WPE > 2)))) void k_wave(WaveLaunch L) {
     using C = typename Store<S>::C;
-    using Sh = WaveShape<S, NS, V>;
+    using Sh = WaveShape<S, NS, VS>;
     static_assert(!(SR && IP), "no stochastic rounding in place");
     static_assert(!(LIST && (SR || IP || GEN)), "lists run two buffers with rounding to nearest");
     constexpr int NG = Sh::NG, NR = NG > 1 ? NG - 1 : 1;  // rings
@@ -534,27 +535,27 @@ __attribute__((amdgpu_waves_per_eu(WaveShape<S, NS, V>::WPE - (GEN && WaveShape<
     const int ya = LIST ? item.ya : sy * L.hs, yb = LIST ? item.yb : min(ya + L.hs, d.ny);
     S* rings = pops + Sh::kPad;
     if constexpr (NG == 1) {
-        wave_group<S, NS, V, SR, IP, GEN, true, true>(L, d, rings, force, 0, xb, sx, sy, ya, yb);
+        wave_group<S, NS, VS, SR, IP, GEN, true, true>(L, d, rings, force, 0, xb, sx, sy, ya, yb);
     } else {
         if (grp == 0)
-            wave_group<S, NS, V, SR, IP, GEN, true, false>(L, d, rings, force, 0, xb, sx, sy, ya, yb);
+            wave_group<S, NS, VS, SR, IP, GEN, true, false>(L, d, rings, force, 0, xb, sx, sy, ya, yb);
         else if (grp == NG - 1)
-            wave_group<S, NS, V, SR, IP, GEN, false, true>(L, d, rings, force, NG - 1, xb, sx, sy, ya, yb);
+            wave_group<S, NS, VS, SR, IP, GEN, false, true>(L, d, rings, force, NG - 1, xb, sx, sy, ya, yb);
         else
-            wave_group<S, NS, V, SR, IP, GEN, false, false>(L, d, rings, force, grp, xb, sx, sy, ya, yb);
+            wave_group<S, NS, VS, SR, IP, GEN, false, false>(L, d, rings, force, grp, xb, sx, sy, ya, yb);
     }
 }
 
 // The kernel of one storage type at ns steps: `run(kernel, threads)`.
-template <typename S, int V, bool SR, bool IP, bool LIST, bool GEN, int NS = 2, typename F>
+template <typename S, int VS, bool SR, bool IP, bool LIST, bool GEN, int NS = 2, typename F>
 void wave_dispatch(int ns, F&& run) {
     constexpr bool kHalf = std::is_same<S, __half>::value;
     // half storage with two columns per lane runs at most four steps, and no
     // type runs 9..11 (a remainder of a sequence takes two launches instead)
-    constexpr int kMax = kHalf ? (V == 2 ? 4 : 8) : 12;
-    if (ns == NS) run(k_wave<S, NS, V, SR, IP, LIST, GEN>, WaveShape<S, NS, V>::NT);
-    else if constexpr (NS < kMax && NS != 8) wave_dispatch<S, V, SR, IP, LIST, GEN, NS + 1>(ns, run);
-    else if constexpr (NS < kMax) wave_dispatch<S, V, SR, IP, LIST, GEN, 12>(ns, run);
+    constexpr int kMax = kHalf ? (VS == 2 ? 4 : 8) : 12;
+    if (ns == NS) run(k_wave<S, NS, VS, SR, IP, LIST, GEN>, WaveShape<S, NS, VS>::NT);
+    else if constexpr (NS < kMax && NS != 8) wave_dispatch<S, VS, SR, IP, LIST, GEN, NS + 1>(ns, run);
+    else if constexpr (NS < kMax) wave_dispatch<S, VS, SR, IP, LIST, GEN, 12>(ns, run);
 }
 
 }  // namespace lbm

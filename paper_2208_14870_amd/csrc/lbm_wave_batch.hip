@@ -11,7 +11,7 @@
 
 namespace lbm_host {
 
-hipError_t launch_wave_list(int prec, int ns, const SlotDesc* slots, const WaveItem* items,
+hipError_t launch_wave_list(int prec, int ns, int v, const SlotDesc* slots, const WaveItem* items,
                             const int* wrange, int nitems, int flip, unsigned grid,
                             hipStream_t st) {
     if (!wave_depth_ok(prec, ns) || nitems < 0 || !items || !wrange || (long long)grid < nitems)
@@ -26,8 +26,11 @@ hipError_t launch_wave_list(int prec, int ns, const SlotDesc* slots, const WaveI
     auto run = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, W);
     };
-    if (prec == LBM_FP64) wave_dispatch<double, 1, false, false, true, false>(ns, run);
+    if (prec == LBM_FP64 && v == 0) wave_dispatch<double, 0, false, false, true, false>(ns, run);
+    else if (prec == LBM_FP64) wave_dispatch<double, 1, false, false, true, false>(ns, run);
+    else if (prec == LBM_FP32 && v == 0) wave_dispatch<float, 0, false, false, true, false>(ns, run);
     else if (prec == LBM_FP32) wave_dispatch<float, 1, false, false, true, false>(ns, run);
+    else if (v == 0) wave_dispatch<__half, 0, false, false, true, false>(ns, run);
     else wave_dispatch<__half, 1, false, false, true, false>(ns, run);
     return hipGetLastError();
 }

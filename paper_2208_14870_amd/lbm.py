@@ -104,6 +104,7 @@ def load() -> ctypes.CDLL:
         "lbm_batch_get_displacement": (i, [vp, i, vp, vp]),
         "lbm_batch_set_tile": (i, [vp, i, i, i]),
         "lbm_batch_info": (i, [vp, pi, ctypes.POINTER(sz), ctypes.POINTER(sz)]),
+        "lbm_batch_get_plain_launch": (i, [vp, i, pi]),
         "lbm_batch_set_time_blocking": (i, [vp, i]),
         "lbm_batch_set_time_blocking_for": (i, [vp, i, i]),
         "lbm_batch_set_wavefront_sites": (i, [vp, i, ll]),
@@ -133,6 +134,15 @@ def _dev_f64(t: torch.Tensor, shape, name: str) -> torch.Tensor:
     if t.dtype != torch.float64 or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != shape:
         raise ValueError(f"{name}: need a contiguous float64 CUDA tensor of shape {shape}")
     return t
+
+
+def _launch_record(out) -> dict:
+    """The record of a lbm_*get_plain_launch."""
+    kind = {0: "tile", 1: "wavefront", 2: "square"}.get(out[1], "single")
+    cfg = {"steps_per_launch": out[0], "kernel": kind, "rows": out[2], "threads": out[3]}
+    if kind == "wavefront":
+        cfg["columns_per_lane"] = out[4]
+    return cfg
 
 
 def _aligned_buffer(nbytes: int, device) -> Tuple[torch.Tensor, int]:
@@ -356,11 +366,7 @@ class Solver:
         workgroup and columns per lane; see lbm_get_plain_launch."""
         out = (ctypes.c_int * 5)()
         self._check(self.lib.lbm_get_plain_launch(self.h, out))
-        kind = {0: "tile", 1: "wavefront", 2: "square"}.get(out[1], "single")
-        cfg = {"steps_per_launch": out[0], "kernel": kind, "rows": out[2], "threads": out[3]}
-        if kind == "wavefront":
-            cfg["columns_per_lane"] = out[4]
-        return cfg
+        return _launch_record(out)
 
     def launch_config(self) -> dict:
         """The nominal shape, which the set_* calls start from (what runs:
@@ -542,6 +548,13 @@ class Batch:
         rule (the lattices a single solver steps through the wavefront)."""
         self._check(self.lib.lbm_batch_set_wavefront_sites(self.h, PRECISIONS[precision],
                                                            int(min_sites)))
+
+    def plain_launch(self, precision: str) -> dict:
+        """What plain steps of a storage type run through at present; see
+        lbm_batch_get_plain_launch."""
+        out = (ctypes.c_int * 5)()
+        self._check(self.lib.lbm_batch_get_plain_launch(self.h, PRECISIONS[precision], out))
+        return _launch_record(out)
 
     def displacements(self, slots):
         """Displacements of several lattices as host arrays [(ux, uy), ...]:

@@ -263,3 +263,45 @@ def test_batched_workload_full_size_sampled(prec):
             np.testing.assert_array_equal(ux, want[0], err_msg=f"lattice {i}")
             np.testing.assert_array_equal(uy, want[1], err_msg=f"lattice {i}")
     b.close()
+
+
+# batches of equal lattices: the list's shape and depth for widths that its strips
+# fit well or badly, totals on both sides of the lines, and lattices that stay with
+# the tile kernel
+EQUAL = [("fp64", 32, 32, 300, "wavefront", 12, 256), ("fp64", 48, 48, 140, "wavefront", 8, 192),
+         ("fp64", 100, 100, 33, "wavefront", 8, 384), ("fp64", 98, 98, 32, "wavefront", 12, 512),
+         ("fp64", 64, 64, 60, "tile", 5, 512), ("fp64", 8, 8, 5000, "tile", 5, 512),
+         ("fp32", 24, 24, 1300, "wavefront", 12, 256), ("fp32", 128, 128, 40, "tile", 8, 512),
+         ("fp32", 100, 100, 80, "wavefront", 8, 384), ("fp16", 48, 44, 1000, "wavefront", 8, 256),
+         ("fp16", 64, 64, 530, "tile", 8, 512)]
+
+
+@pytest.mark.parametrize("prec,nx,ny,count,kernel,depth,threads", EQUAL)
+def test_batch_of_equal_lattices_takes_the_shape_that_fits(prec, nx, ny, count, kernel, depth, threads):
+    """The kernel, depth and workgroup of a batch of equal lattices, and the
+    displacement of three of them after plain steps (full launches and
+    remainders) and a check, against solo single steps bit for bit."""
+    from paper_2208_14870_amd import lbm
+    need_gpu()
+    say(f"batch of {count} {nx}x{ny} {prec}")
+    mat = P.Material.from_shear_poisson(0.9, 0.3)
+    b = lbm.Batch(count, int(count * (lbm.Batch.slot_bytes(nx, ny, prec) * 1.2 + 100000)) + GIB)
+    loads = [_load(nx, ny, 300 + k) for k in range(3)]
+    dl = [(dev(gx), dev(gy)) for gx, gy in loads]
+    slots = [b.add(nx, ny, mat.lame_lambda, mat.lame_mu, *dl[k % 3], prec) for k in range(count)]
+    got = b.plain_launch(prec)
+    assert (got["kernel"], got["steps_per_launch"], got["threads"]) == (kernel, depth, threads), got
+    done = 0
+    for n, check in ((depth, False), (2 * depth + 7, False), (13, True), (11, False), (3, False)):
+        b.step(n, check=check)
+        done += n
+    for k in (0, count // 3 * 3 - 2, count - 1):
+        want = _solo(nx, ny, prec, mat, *loads[k % 3], done)
+        got = [host(t) for t in b.displacement(slots[k])]
+        if prec == "fp16":
+            sc = max(np.max(np.abs(want[0])), np.max(np.abs(want[1])), 1e-300)
+            assert max(np.max(np.abs(got[0] - want[0])), np.max(np.abs(got[1] - want[1]))) <= 1e-9 * sc
+        else:
+            np.testing.assert_array_equal(got[0], want[0])
+            np.testing.assert_array_equal(got[1], want[1])
+    b.close()
