@@ -138,7 +138,9 @@ struct lbm_solver {
     // as given (higher only where a launch would hold too many threads).
     void make_plan() {
         plan = PlainPlan();
+        L.single = false;
         choose_plan();
+        L.single = plan.single;
         if (plan.wave)
             plan.hs = std::max(plan.hs, wave_least_rows(L.prec, plan.ns, plan.v, L.nx, L.ny));
     }
@@ -148,25 +150,42 @@ struct lbm_solver {
             if (!L.ip_blocked()) return;
             plan = inplace_plan(prec, L.nx, L.ny, L.tb, L.wave_v, L.wave_hs, fused_auto, depth_auto,
                                 L.halo_cap, cus,
-                                [&](int ns) { return wave_blocks_per_cu(prec, ns, L.wave_v); });
+                                [&](int ns, int v) { return wave_blocks_per_cu(prec, ns, v); });
             return;
         }
         const bool gen = L.general();
         if (L.tb < 2 || (gen ? L.sr_on() || (!fused_auto && L.wave_hs == 0) : !L.fused())) return;
         const bool chosen = !fused_auto || !depth_auto || L.th_user > 0;
         const int sq = chosen ? 0 : square_depth(L.nx, L.ny, cus);
-        if (!gen && (chosen ? L.wave_hs == 0 : !wave_auto(prec, L.N, L.sr_on()) && sq == 0 && L.tile_fits()))
-            return;
         if (sq > 0) {
             plan.square = true;
             plan.ns = sq;
             return;
         }
-        if (!L.wave_fits()) return;
-        plan.wave = true;
+        if (!chosen && (gen || wave_auto(prec, L.N, L.sr_on())) &&
+            thin_lattice(prec, L.nx, L.ny, gen)) {
+            plan.single = true;
+            return;
+        }
         plan.ns = depth_auto && fused_auto ? wave_depth(prec) : L.tb;
         plan.v = depth_auto && fused_auto && !gen ? wave_cols_deep(prec, L.nx, L.ny)
                                                   : wave_cols(prec, plan.ns, L.nx, L.ny);
+        auto cost = [&](int v, int ns) { return wave_cost(prec, v, ns, L.nx, L.ny); };
+        if (plan.v == 1) {
+            if (chosen) plan.v = wave_best_width(plan.ns, cost);
+            else wave_best_shape(prec, cost, plan.v, plan.ns);
+        }
+        // half storage by cost, and FP64 lattices of a few rows (60000 x 3: tile 3.6 us
+        // per step, wavefront 4.5); the other types' tiles lose to the wavefront there
+        const bool by_cost = prec == LBM_FP16 ||
+                             (prec == LBM_FP64 && L.ny < 8 && L.wave_hs == 0);
+        const bool tiles = L.tile_fits() &&
+                           (!wave_auto(prec, L.N, L.sr_on()) ||
+                            (by_cost && !wave_over_tile(cost(plan.v, plan.ns),
+                                                        tile_cost(prec, L.nx, L.ny))));
+        if (!gen && (chosen ? L.wave_hs == 0 : tiles)) return;
+        if (!L.wave_fits()) return;
+        plan.wave = true;
         const int w = wave_out(plan.ns, plan.v, is_half(prec));
         const long long strips = (L.nx + w - 1) / w;
         plan.hs = fused_auto ? wave_segment_rows(plan.ns, cus, wave_blocks_per_cu(prec, plan.ns, plan.v),
@@ -814,7 +833,7 @@ int lbm_set_tile_rows(lbm_solver* s, int rows) {
     Lattice& L = s->L;
     if (rows != 0 && !(rows == 8 || rows == 12 || rows == 16 || rows == 24))
         return s->fail(LBM_E_ARG, "set_tile_rows: rows must be 0, 8, 12, 16 or 24");
-    if (rows != 0 && L.fused() && L.wave_hs == 0 && !stepN_supported(L.prec, L.tb, rows))
+    if (rows != 0 && L.blocks() && L.wave_hs == 0 && !stepN_supported(L.prec, L.tb, rows))
         return s->fail(LBM_E_ARG, "set_tile_rows: no tile kernel of that height for this "
                                   "storage type and steps per launch");
     L.th_user = rows;
@@ -877,7 +896,7 @@ int lbm_get_launch_config(const lbm_solver* s, int out[4]) {
         out[1] = LBM_FUSED_WAVEFRONT;
         out[2] = L.wave_hs;
         out[3] = kBlock;
-    } else if (!L.fused()) {
+    } else if (!L.blocks()) {
         out[1] = -1;
         out[2] = L.inplace ? 0 : L.eff_vy();
         out[3] = kBlock;
@@ -908,7 +927,7 @@ int lbm_get_plain_launch(const lbm_solver* s, int out[5]) {
         out[1] = LBM_FUSED_WAVEFRONT;
         out[2] = p.hs;
         out[3] = wave_threads(p.ns, p.v, is_half(L.prec));
-        out[4] = p.v;
+        out[4] = wave_lane_cols(p.v);
     } else if (L.fused()) {
         out[0] = L.tb;
         out[1] = LBM_FUSED_TILE;
@@ -925,7 +944,7 @@ int lbm_get_plain_launch(const lbm_solver* s, int out[5]) {
 
 int lbm_get_wave_columns(const lbm_solver* s) {
     if (!s) return LBM_E_ARG;
-    return ((s->L.fused() && s->L.wave_hs > 0) || s->L.ip_blocked()) ? s->L.wave_v : 0;
+    return ((s->L.blocks() && s->L.wave_hs > 0) || s->L.ip_blocked()) ? s->L.wave_v : 0;
 }
 
 int lbm_step(lbm_solver* s, long long nsteps) {

@@ -418,6 +418,7 @@ inline size_t ip_halo_bytes(int prec, int ns, int nx, int ny, int hs = 0) {
 struct PlainPlan {
     bool wave = false;
     bool square = false;  // the small-lattice kernel
+    bool single = false;  // one step per launch where the nominal shape has more
     int ns = 0, v = 1, hs = 0;
 };
 
@@ -534,26 +535,37 @@ inline int square_depth(int nx, int ny, int cus) {
         if (square_tiles(ns, nx, ny) <= cus) return ns;
     return 0;
 }
+// Lattices that run one step per launch although nothing is chosen: one row, and
+// with free rates few rows or columns.  Blocked launches there spend their time on
+// halo rows and idle columns (us per step, blocked / single: 1000000 x 1 FP64 56.6
+// / 25.9, FP32 28.1 / 13.2, FP16 36.9 / 11.0; free rates 3 x 500000 FP64 77 / 58, 8 x
+// 50000 FP64 9.9 / 14.1, FP32 6.8 / 8.3, FP16 9.2 / 6.0, 16 x 20000 FP16 5.2 / 4.9,
+// 500000 x 3 FP32 22.0 / 20.5, 400000 x 4 18.4 / 20.7).
+inline bool thin_lattice(int prec, int nx, int ny, bool general) {
+    return ny < 2 || (general && (nx < (prec == LBM_FP16 ? 20 : 8) || ny < 4));
+}
 inline int wave_depth(int prec) { return prec == LBM_FP16 ? 8 : 12; }
 // Plain steps in place: tb steps per launch over segments of hs rows, v columns
 // per lane.  A height that the library picked (auto_rows) gives way to a longer
 // one (fewer row copies), and eight steps that it picked (auto_depth) to twelve
 // where the longer segments leave the room, which is that of the nominal height
-// (FP32 4096 x 3000 2558 us for 64 steps at eight, 2330 at twelve).  per_cu(ns):
-// workgroups that a compute unit holds.
+// (FP32 4096 x 3000 2558 us for 64 steps at eight, 2330 at twelve).  Strips of one
+// wave where they suit the width, which need the same room at the nominal depth.
+// per_cu(ns, v): workgroups that a compute unit holds.
 template <typename F>
 inline PlainPlan inplace_plan(int prec, int nx, int ny, int tb, int v, int hs, bool auto_rows,
                               bool auto_depth, size_t room, int cus, F&& per_cu) {
     PlainPlan p;
     p.wave = true;
     p.ns = tb;
-    p.v = v;
+    auto cost = [&](int cv, int ns) { return wave_cost(prec, cv, ns, nx, ny); };
+    p.v = v = v == 1 ? wave_best_width(tb, cost) : v;
     p.hs = hs;
     if (!auto_rows) return p;
     auto rows = [&](int ns) {
         const int w = wave_out(ns, v, is_half(prec));
         const long long strips = ((long long)nx + w - 1) / w;
-        return wave_segment_rows(ns, cus, per_cu(ns), hs, ny,
+        return wave_segment_rows(ns, cus, per_cu(ns, v), hs, ny,
                                  [&](int h) { return strips * ((ny + h - 1) / h); });
     };
     p.hs = rows(tb);
@@ -738,6 +750,7 @@ struct Lattice {
     int th_user = 0;  // tile height chosen by the caller (0: the default)
     int wave_hs = 0;  // > 0: fused launches use the wavefront, segments of wave_hs rows
     int wave_v = 1;   // the wavefront's columns per lane
+    bool single = false;  // one step per launch, whatever the shape (thin_lattice)
     int cur = 0;      // buffer with the state at flip 0
     bool inplace = false;  // one buffer, in-place streaming (layout alternates per step)
     void* halo = nullptr;  // in place: room for the wavefront's halo copies
@@ -758,9 +771,10 @@ struct Lattice {
     bool tile_fits() const { return plane * (long long)arith_bytes(prec) <= 0xFFFFFFFFLL; }
     // The wavefront addresses a row with them; wider rows run one step per launch.
     bool wave_fits() const { return wave_row_ok(prec, nx); }
-    bool fused() const {
+    bool blocks() const {
         return tb >= 2 && !general() && !inplace && (wave_hs > 0 ? wave_fits() : tile_fits());
     }
+    bool fused() const { return blocks() && !single; }
     // in place, up to tb steps per launch through the in-place wavefront
     bool ip_blocked() const {
         return inplace && tb >= 2 && !general() && wave_hs > 0 && wave_fits();

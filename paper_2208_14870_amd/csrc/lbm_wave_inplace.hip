@@ -46,10 +46,13 @@ hipError_t launch_wave_inplace(int prec, int ns, int v, int nx, int ny, int hs,
     auto run = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, W);
     };
-    if (prec == LBM_FP64) wave_dispatch<double, 1, false, true, false, false>(ns, run);
+    if (prec == LBM_FP64 && v == 0) wave_dispatch<double, 0, false, true, false, false>(ns, run);
+    else if (prec == LBM_FP64) wave_dispatch<double, 1, false, true, false, false>(ns, run);
     else if (prec == LBM_FP32 && v == 2) wave_dispatch<float, 2, false, true, false, false>(ns, run);
+    else if (prec == LBM_FP32 && v == 0) wave_dispatch<float, 0, false, true, false, false>(ns, run);
     else if (prec == LBM_FP32) wave_dispatch<float, 1, false, true, false, false>(ns, run);
     else if (v == 2) wave_dispatch<__half, 2, false, true, false, false>(ns, run);
+    else if (v == 0) wave_dispatch<__half, 0, false, true, false, false>(ns, run);
     else wave_dispatch<__half, 1, false, true, false, false>(ns, run);
     return hipGetLastError();
 }

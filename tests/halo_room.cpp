@@ -14,7 +14,7 @@ static void look(int prec, int nx, int ny, int tb, int hs, bool auto_rows, bool 
                  size_t room, int per_cu) {
     const int v = ip_wave_cols(prec, tb, nx);
     PlainPlan p = inplace_plan(prec, nx, ny, tb, v, hs, auto_rows, auto_depth, room, 256,
-                               [&](int) { return per_cu; });
+                               [&](int, int) { return per_cu; });
     p.hs = std::max(p.hs, wave_least_rows(prec, p.ns, p.v, nx, ny));
     ++plans;
     deep += p.ns > 8;

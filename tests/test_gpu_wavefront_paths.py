@@ -90,3 +90,40 @@ def test_in_place_at_twelve_steps(prec, nx, ny, v):
     """In place at the default depth, from both layouts, with remainders of every
     kind."""
     _same(nx, ny, prec, (13, 12, 23, 24, 35, 1, 12), None, (12, v), inplace=True)
+
+
+# strips of one wave: widths at its output columns (40 at twelve steps, 48 at
+# eight), one beyond, and far below; by default, with free rates, in place (odd
+# widths, or FP64) and with stochastic rounding
+NARROW = [("fp64", 40, 5000, 12, 256, ""), ("fp64", 48, 4000, 8, 192, ""), ("fp64", 3, 90001, 12, 256, ""),
+          ("fp32", 39, 10007, 12, 256, ""), ("fp32", 40, 9001, 12, 256, ""), ("fp32", 47, 9000, 8, 192, ""),
+          ("fp32", 1, 400003, 12, 256, ""), ("fp16", 48, 30011, 8, 256, ""), ("fp16", 5, 300001, 8, 256, ""),
+          ("fp64", 40, 5000, 12, 256, "rates"), ("fp64", 48, 4000, 8, 192, "rates"),
+          ("fp32", 8, 50000, 12, 256, "rates"), ("fp32", 47, 9000, 8, 192, "rates"),
+          ("fp16", 48, 9001, 8, 256, "rates"), ("fp16", 20, 20011, 8, 256, "rates"),
+          ("fp64", 48, 4000, 8, 192, "in place"), ("fp64", 3, 9001, 8, 192, "in place"),
+          ("fp32", 39, 10007, 8, 192, "in place"), ("fp16", 48, 3001, 8, 256, "in place"),
+          ("fp16", 47, 50000, 8, 256, "stochastic")]
+
+
+@pytest.mark.parametrize("prec,nx,ny,depth,threads,kind", NARROW)
+def test_narrow_lattices_take_strips_of_one_wave(prec, nx, ny, depth, threads, kind):
+    """Lattices no wider than a strip of one wave: full launches and every
+    remainder."""
+    def shape(s):
+        p = s.plain_launch()
+        assert (p["kernel"], p["steps_per_launch"], p["threads"]) == ("wavefront", depth, threads), p
+    _same(nx, ny, prec, (depth, 7, 2 * depth + 5, 11, 3), shape,
+          rates=RATES if kind == "rates" else None, sr=kind == "stochastic",
+          inplace=kind == "in place")
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("nx,ny,depth,rows", [(40, 30, 8, 7), (48, 9, 8, 16), (60, 12, 2, 5), (33, 70, 5, 64)])
+def test_chosen_wavefront_on_narrow_lattices(prec, nx, ny, depth, rows):
+    """A chosen depth and segment height on lattices no wider than one wave."""
+    def shape(s):
+        s.set_time_blocking(depth)
+        s.set_fused_kernel("wavefront", rows)
+        assert s.plain_launch()["steps_per_launch"] == depth
+    _same(nx, ny, prec, (depth, 2 * depth + 1, 3), shape)
