@@ -186,6 +186,8 @@ struct lbm_solver {
         if (!gen && (chosen ? L.wave_hs == 0 : tiles)) return;
         if (!L.wave_fits()) return;
         plan.wave = true;
+        if (!chosen && !gen && plan.v == 1 && L.wave_hs == 0 && L.tile_fits())
+            tile_remainders(prec, L.N, plan);
         const int w = wave_out(plan.ns, plan.v, is_half(prec));
         const long long strips = (L.nx + w - 1) / w;
         plan.hs = fused_auto ? wave_segment_rows(plan.ns, cus, wave_blocks_per_cu(prec, plan.ns, plan.v),
@@ -205,7 +207,7 @@ struct lbm_solver {
         const int d = depth();
         if (rem >= d) return d;
         if (plan.square) return (int)std::max(1LL, rem);
-        if (plan.wave) return rem <= 8 ? (int)std::max(1LL, rem) : (rem == 9 ? 5 : 8);
+        if (plan.wave) return rem <= 8 ? (int)std::max(1LL, rem) : (int)(rem + 1) / 2;
         return (rem >= 2 && stepN_supported(L.prec, (int)rem, L.th)) ? (int)rem : 1;
     }
 
@@ -265,8 +267,10 @@ struct lbm_solver {
 
     // One fused launch of ns steps (a full launch, or a shorter remainder).
     hipError_t enqueue_fused(int ns, hipStream_t st, long long& ph) {
+        const bool tile = ns < plan.ns && ns >= plan.tile_from && ns <= plan.tile_to &&
+                          stepN_supported(L.prec, ns, L.th);
         hipError_t e =
-            plan.wave
+            plan.wave && !tile
                 ? launch_wave(L.prec, ns, plan.v, L.nx, L.ny, plan.hs, d_desc, (int)(ph & 1), st,
                               L.sr_on(), L.general())
             : plan.square
@@ -342,13 +346,15 @@ struct lbm_solver {
 
     // Steps of the fused launch that ends a sequence of n steps whose last two
     // are a write-u step and a check step (two buffers, LDS tile kernel over the
-    // tile work list): with plain launches of d steps the remainder of n, so
-    // that the plain part is whole launches, at least 2 (a full launch when n is
-    // a multiple); after wavefront launches, which are faster per step, two to
-    // five, such that what they leave is one wavefront launch or none.  0 when
-    // that launch has no kernel (the two steps then run one per launch; FP64
-    // 1023 x 770: 61 us for the two, 105 for a tile launch of eight that carries
-    // them, 45 for one of four).
+    // tile work list): the remainder of n, so that the plain part is whole
+    // launches, at least 2 (a full launch when n is a multiple).  After wavefront
+    // launches, which are faster per step, a long remainder is split between a
+    // wavefront launch and four steps with the check, and a multiple as well; the
+    // line is where that pays (us for 5, 6, 8 steps, one tile launch / split: FP64
+    // 660^2 42.5 54.9 60.7 / 55.9 56.3 57.8; FP32 1000^2 44.6 48.8 54.3 / 61.6 62.4
+    // 64.9; FP16 2100^2 121 127 158 / 154 176 168).  0 when that launch has no
+    // kernel (the two steps then run one per launch; FP64 1023 x 770: 61 us for the
+    // two, 45 for a tile launch of four that carries them).
     int check_span(long long n) const {
         if (plan.square) {  // its own check launch, the remainder of n, at least 2
             const int d = plan.ns;
@@ -360,7 +366,10 @@ struct lbm_solver {
         const int d = depth();
         const long long r = n % d;
         long long k = r >= 2 ? r : d;
-        if (plan.wave) k = (r >= 2 && r <= 4) ? r : r == 1 ? 5 : r == 5 ? 3 : 4;
+        if (plan.wave) {
+            const int most = L.prec == LBM_FP64 ? 5 : 8;
+            k = r == 0 ? (d <= most ? d : 4) : r == 1 ? 5 : r <= most ? r : 4;
+        }
         while (plan.wave && k > 2 && (k > n || !stepN_supported(L.prec, (int)k, L.th))) --k;
         return (k <= n && stepN_supported(L.prec, (int)k, L.th)) ? (int)k : 0;
     }

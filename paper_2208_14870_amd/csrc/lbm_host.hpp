@@ -420,6 +420,7 @@ struct PlainPlan {
     bool square = false;  // the small-lattice kernel
     bool single = false;  // one step per launch where the nominal shape has more
     int ns = 0, v = 1, hs = 0;
+    int tile_from = 9, tile_to = 0;  // remainders that run through the tile kernel instead
 };
 
 // Time of a row of a wavefront's workgroup, by shape (v, see lbm_wave_shape.hpp)
@@ -519,6 +520,16 @@ inline bool wave_auto(int prec, long long n, bool sr) {
     if (prec == LBM_FP64) return n >= 150000;
     if (prec == LBM_FP32) return n >= 327680;
     return n >= (sr ? 1LL << 21 : 1LL << 20);
+}
+// Remainders of these lattices that the tile kernel runs faster (us, wavefront /
+// tile: FP64 450^2 four steps 12.1 / 9.1, five 13.2 / 11.1, six 14.4 / 15.6, 570^2
+// five 17.2 / 18.6; FP32 600^2 three 12.7 / 11.9, six 15.7 / 13.7, seven 15.1 / 15.0,
+// 850^2 five 19.3 / 18.8; FP16 1200^2 three 21.9 / 20.8, 1500^2 29.6 / 33.4, 2100^2
+// two 60.4 / 59.2, 4000^2 229 / 190).
+inline void tile_remainders(int prec, long long n, PlainPlan& p) {
+    if (prec == LBM_FP64 && n < 300000) p.tile_from = 4, p.tile_to = 5;
+    else if (prec == LBM_FP32 && n < 600000) p.tile_from = 3, p.tile_to = 6;
+    else if (prec == LBM_FP16) p.tile_from = 2, p.tile_to = n < 1600000 ? 3 : 2;
 }
 // Tiles of the small-lattice kernel (k_stepS) at ns steps per launch, and the
 // depth it runs at: the deepest of 4..12 whose tiles are no more than the

@@ -127,3 +127,37 @@ def test_chosen_wavefront_on_narrow_lattices(prec, nx, ny, depth, rows):
         s.set_fused_kernel("wavefront", rows)
         assert s.plain_launch()["steps_per_launch"] == depth
     _same(nx, ny, prec, (depth, 2 * depth + 1, 3), shape)
+
+
+# the smallest lattices of the default rule (150000, 327680, 2^20 sites, 2^21 with
+# stochastic rounding), whose short remainders and checks run through the tile
+# kernel, and larger ones, whose do not
+@pytest.mark.parametrize("prec,nx,ny,sr", [("fp64", 5000, 31, False), ("fp64", 450, 449, False),
+                                           ("fp64", 570, 570, False), ("fp32", 600, 548, False),
+                                           ("fp32", 701, 700, False), ("fp32", 850, 849, False),
+                                           ("fp16", 1024, 1025, False), ("fp16", 1500, 1400, True)])
+def test_short_calls_at_the_default_rule(prec, nx, ny, sr):
+    """Calls of 2..11 steps, and checked calls of 2..21: states equal single
+    steps', residuals up to the order of their sums (2^-53 per addition)."""
+    from paper_2208_14870_amd import lbm
+    _same(nx, ny, prec, tuple(range(2, 12)), None, (8 if prec == "fp16" else 12, 1), sr=sr)
+    mat = P.Material.from_shear_poisson(0.9, 0.3)
+    rng = np.random.default_rng(5)
+    f0 = dev(rng.standard_normal((8, ny, nx)))
+    g = rng.standard_normal((2, ny, nx)) * 1e-2
+    g = [dev(a - a.mean()) for a in g]
+    res = []
+    for single in (False, True):
+        s = lbm.Solver(nx, ny, prec)
+        s.set_material(mat.lame_lambda, mat.lame_mu)
+        if sr:
+            s.set_stochastic_rounding(True, 7)
+        s.set_body_force(*g)
+        s.set_populations(f0)
+        if single:
+            s.set_time_blocking(1)
+        r = [s.step_checked(n) for n in range(2, 22)]
+        res.append((r, host(s.populations())))
+        s.close()
+    np.testing.assert_array_equal(res[0][1], res[1][1])
+    np.testing.assert_allclose(res[0][0], res[1][0], rtol=nx * ny * 2.0 ** -52, atol=0)
