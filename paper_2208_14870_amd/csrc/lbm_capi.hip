@@ -156,7 +156,10 @@ struct lbm_solver {
         const bool gen = L.general();
         if (L.tb < 2 || (gen ? L.sr_on() || (!fused_auto && L.wave_hs == 0) : !L.fused())) return;
         const bool chosen = !fused_auto || !depth_auto || L.th_user > 0;
-        const int sq = chosen ? 0 : square_depth(L.nx, L.ny, cus);
+        // free rates have no tile kernel: a chosen depth on a small lattice as well
+        const int sq = !chosen ? square_depth(L.nx, L.ny, cus)
+                       : gen && fused_auto && L.th_user == 0 && square_tiles(L.tb, L.nx, L.ny) <= cus
+                           ? L.tb : 0;
         if (sq > 0) {
             plan.square = true;
             plan.ns = sq;

@@ -161,3 +161,16 @@ def test_short_calls_at_the_default_rule(prec, nx, ny, sr):
         s.close()
     np.testing.assert_array_equal(res[0][1], res[1][1])
     np.testing.assert_allclose(res[0][0], res[1][0], rtol=nx * ny * 2.0 ** -52, atol=0)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("nx,ny", [(100, 100), (31, 57), (3, 5)])
+def test_general_rates_at_a_chosen_depth_on_small_lattices(prec, nx, ny):
+    """Free rates have no tile kernel: a chosen depth runs through the
+    small-lattice kernel where its tiles are no more than the compute units."""
+    for depth in range(2, 9):
+        def shape(s):
+            s.set_time_blocking(depth)
+            p = s.plain_launch()
+            assert (p["kernel"], p["steps_per_launch"]) == ("square", depth), p
+        _same(nx, ny, prec, (depth, 2 * depth + depth // 2, 3), shape, rates=RATES)
