@@ -415,11 +415,11 @@ struct lbm_batch {
 
     // Steps of the next launch of precision p when `rem` plain steps are left: a
     // full launch, else the remainder as one shorter launch where kernels exist
-    // for it (up to eight steps; 9..11 as two launches), else a single step.
+    // for it (up to eight steps; 9..11 in halves), else a single step.
     int next_span(int p, long long rem) const {
         if (tb[p] < 2) return 1;
         if (rem >= tb[p]) return tb[p];
-        if (rem > 8) return rem == 9 ? 5 : 8;
+        if (rem > 8) return (int)(rem + 1) / 2;
         return (rem >= 2 && stepN_supported(p, (int)rem, th[p])) ? (int)rem : 1;
     }
 
@@ -435,14 +435,14 @@ struct lbm_batch {
     // ordinary launches, then one fused launch of `span` steps whose last two
     // steps form the residual check (span 0: a write-u step and a check step,
     // one step per launch).  The span makes the plain part whole launches: the
-    // remainder of n (at least 2), else a full launch of up to eight steps, four
-    // after launches of twelve.
+    // remainder of n (at least 2), else a full launch of up to eight steps; after
+    // launches of twelve four, or five that leave eight (n = 13: one launch less).
     void check_plan(int p, long long n, long long& plain, int& span) const {
         plain = n - 2;
         span = 0;
         if (tb[p] < 2) return;
         const long long r = n % tb[p];
-        const long long k = (r >= 2 && r <= 8) ? r : tb[p] <= 8 ? tb[p] : 4;
+        const long long k = (r >= 2 && r <= 8) ? r : tb[p] <= 8 ? tb[p] : r == 1 ? 5 : 4;
         if (k > n || !stepN_supported(p, (int)k, th[p])) return;
         plain = n - k;
         span = (int)k;

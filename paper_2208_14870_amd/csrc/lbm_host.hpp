@@ -448,10 +448,11 @@ inline double tile_cost(int prec, int nx, int ny) {
     return tiles * (prec == LBM_FP64 ? 1.19 : prec == LBM_FP32 ? 2.09 : 2.06);
 }
 // Whether lattices of these costs run faster through the wavefront.  The costs
-// are those of a full chip; up to 0.86 the wavefront was the faster one at every
+// are those of a full chip; up to 0.82 the wavefront was the faster one at every
 // total above batch_wave_total (FP32 56^2 0.80: 1.01 to 1.09 times as fast; FP32
-// 64^2 0.88: 0.80 to 1.10; FP16 128^2 0.88: 0.94 to 1.12).
-inline bool wave_over_tile(double wave, double tile) { return wave < 0.86 * tile; }
+// 64^2 0.88: 0.80 to 1.10; FP16 128^2 0.88: 0.94 to 1.12, lattices of 48..160 a side
+// 0.84: 0.95).
+inline bool wave_over_tile(double wave, double tile) { return wave < 0.82 * tile; }
 // Shape and depth of the wavefront that takes the least time for the lattices of
 // total(v, ns): two waves per strip at the library's depth unless another is
 // clearly better.  Strips leave columns idle where they do not divide a width:
