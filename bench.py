@@ -558,7 +558,7 @@ def sweep_batched(cases, nchunks: int, chunk: int, warm: int = 1):
 
 def batch_run(prec: str, nlat: int = 512, steps: int = 2000, chunk: int = 100):
     """Batched workload: `nlat` lattices (seed 4, sides {64..512}, nu ~ U[0.05, 0.48]),
-    one launch per step over the tile work list, graph-replayed chunks with a
+    all of them in each launch of several steps (the tuner's choice), with a
     residual check at the end of each chunk."""
     import torch
     from paper_2208_14870_amd import autotune, lbm, problem as P
@@ -570,6 +570,7 @@ def batch_run(prec: str, nlat: int = 512, steps: int = 2000, chunk: int = 100):
         b.add(c.nx, c.ny, c.material.lame_lambda, c.material.lame_mu,
               torch.from_numpy(c.gx).cuda(), torch.from_numpy(c.gy).cuda(), prec)
     shape = autotune.tune_batch(b, prec, sites)
+    launch = b.plain_launch(prec)
     b.step(chunk, check=True)
     torch.cuda.synchronize()
     e0 = torch.cuda.Event(enable_timing=True)
@@ -585,14 +586,14 @@ def batch_run(prec: str, nlat: int = 512, steps: int = 2000, chunk: int = 100):
     n = steps // chunk * chunk
     us = 1e3 * e0.elapsed_time(e1) / n
     b.close()
-    # population passes per chunk: fused launches of shape[3] steps (the last
-    # carrying the residual check); approximate for the check's own split
-    tb = max(1, int(shape[3])) if len(shape) > 3 else 1
+    # population passes per chunk: full launches (the last carrying the residual
+    # check); approximate for the check's own split
+    tb = max(1, launch["steps_per_launch"])
     passes = math.ceil(chunk / tb)
     min_bytes = BYTES_PER_SITE[prec] * sites
     achieved = min_bytes * passes / chunk / (us * 1e-6) / 1e9
     return {"lattices": nlat, "sites": sites, "steps": n, "mlups": sites * n / wall / 1e6,
-            "us_per_step": round(us, 2), "tile": list(shape),
+            "us_per_step": round(us, 2), "tile": list(shape), "launch": launch,
             "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                          "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                          "min_bytes_per_pass": min_bytes, "passes_per_chunk": passes,

@@ -407,6 +407,11 @@ enum lbm_fused_kernel {
  * place, the segment height needs more halo room than the workspace has). */
 int lbm_set_fused_kernel(lbm_solver *s, int kind, int segment_rows);
 
+/* Gives the launch shape back to the library, as if none of lbm_set_tile,
+ * lbm_set_time_blocking, lbm_set_tile_rows and lbm_set_fused_kernel had been
+ * called.  Errors: LBM_E_ARG. */
+int lbm_set_launch_auto(lbm_solver *s);
+
 /* Optional, half storage (LBM_FP16) with two buffers: on = 1 rounds every
  * stored population (HBM and the fused kernel's LDS copies) stochastically
  * instead of to nearest: up with probability equal to the discarded fraction
@@ -539,6 +544,12 @@ int lbm_batch_get_displacement(lbm_batch *b, int slot, double *ux, double *uy);
 /* Launch shape for all lattices of the batch (see lbm_set_tile; bx_log2 in
  * 3..8). */
 int lbm_batch_set_tile(lbm_batch *b, int bx_log2, int rows_per_thread, int blocks_per_cu);
+
+/* Gives the launch shape of one storage type (steps per launch, wavefront list)
+ * and the tile shape of single steps back to the library, as if none of
+ * lbm_batch_set_time_blocking(_for), lbm_batch_set_wavefront_sites and
+ * lbm_batch_set_tile had been called.  Errors: LBM_E_ARG, LBM_E_HIP. */
+int lbm_batch_set_launch_auto(lbm_batch *b, int precision);
 
 /* What plain steps of a storage type run through at present, as
  * lbm_get_plain_launch (out[1] LBM_FUSED_WAVEFRONT once lattices are on the

@@ -742,6 +742,19 @@ int lbm_batch_set_time_blocking_for(lbm_batch* b, int precision, int steps_per_l
     return b->rebuild();
 }
 
+int lbm_batch_set_launch_auto(lbm_batch* b, int precision) {
+    if (!b) return LBM_E_ARG;
+    if (!valid_prec(precision))
+        return b->fail(LBM_E_ARG, "batch_set_launch_auto: precision LBM_FP64/FP32/FP16");
+    b->tb_auto[precision] = true;
+    b->wave_min[precision] = -1;
+    b->bx_log2 = 6;
+    b->vy = 2;
+    b->blocks_per_cu = 0;
+    b->drop_graphs();
+    return b->rebuild();
+}
+
 int lbm_batch_set_wavefront_sites(lbm_batch* b, int precision, long long min_sites) {
     if (!b) return LBM_E_ARG;
     if (!valid_prec(precision) || min_sites < -1)

@@ -132,6 +132,22 @@ struct lbm_solver {
         fused_auto = depth_auto = true;
     }
 
+    // In place: room beyond the minimal workspace holds the wavefront's halo copies,
+    // and the deepest launch whose default shape fits is the default.
+    void default_inplace() {
+        L.tb = 1;
+        L.th = fused_th(L.prec, 1, L.N);
+        L.wave_hs = 0;
+        L.wave_v = 1;
+        for (int k = 8; k >= 2; --k) {
+            if (ip_halo_bytes(L.prec, k, L.nx, L.ny) > L.halo_cap) continue;
+            L.tb = k;
+            L.wave_v = ip_wave_cols(L.prec, k, L.nx);
+            L.wave_hs = ip_segment_rows(k, L.wave_v, L.nx, L.ny);
+            break;
+        }
+    }
+
     // The launches of plain steps.  Left to the library, large lattices and all
     // lattices with free rates run through the wavefront at its own depth and
     // segment height; a depth, kernel or height that the caller chose is taken
@@ -558,22 +574,9 @@ static int create_solver(int nx, int ny, int precision, int with_polish, bool in
     L.inplace = inplace;
     s->default_shape();
     if (inplace) {
-        L.tb = 1;
-        L.th = fused_th(precision, 1, L.N);
-        L.wave_hs = 0;
-        L.wave_v = 1;
-        // room beyond the minimum holds the in-place wavefront's halo copies:
-        // the deepest launch whose default shape fits is the default
         L.halo = reinterpret_cast<char*>(workspace) + need;
         L.halo_cap = (workspace_bytes_given - need) / kAlign * kAlign;
-        for (int k = 8; k >= 2; --k) {
-            if (ip_halo_bytes(precision, k, nx, ny) <= L.halo_cap) {
-                L.tb = k;
-                L.wave_v = ip_wave_cols(precision, k, nx);
-                L.wave_hs = ip_segment_rows(k, L.wave_v, nx, ny);
-                break;
-            }
-        }
+        s->default_inplace();
     }
     char* base = reinterpret_cast<char*>(workspace);
     size_t off = 0;
@@ -887,6 +890,14 @@ int lbm_set_fused_kernel(lbm_solver* s, int kind, int segment_rows) {
     } else {
         return s->fail(LBM_E_ARG, "set_fused_kernel: kind must be LBM_FUSED_TILE or LBM_FUSED_WAVEFRONT");
     }
+    return s->sync_desc();
+}
+
+int lbm_set_launch_auto(lbm_solver* s) {
+    if (!s) return LBM_E_ARG;
+    s->blocks_per_cu = 0;
+    s->default_shape();
+    if (s->L.inplace) s->default_inplace();
     return s->sync_desc();
 }
 

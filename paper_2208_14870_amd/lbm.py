@@ -86,6 +86,7 @@ def load() -> ctypes.CDLL:
         "lbm_get_launch_config": (i, [vp, pi]),
         "lbm_get_plain_launch": (i, [vp, pi]),
         "lbm_get_wave_columns": (i, [vp]),
+        "lbm_set_launch_auto": (i, [vp]),
         "lbm_workspace_bytes_inplace": (sz, [i, i, i]),
         "lbm_workspace_bytes_inplace_blocked": (sz, [i, i, i, i, i]),
         "lbm_create_inplace": (i, [i, i, i, vp, sz, vp, ctypes.POINTER(vp)]),
@@ -105,6 +106,7 @@ def load() -> ctypes.CDLL:
         "lbm_batch_set_tile": (i, [vp, i, i, i]),
         "lbm_batch_info": (i, [vp, pi, ctypes.POINTER(sz), ctypes.POINTER(sz)]),
         "lbm_batch_get_plain_launch": (i, [vp, i, pi]),
+        "lbm_batch_set_launch_auto": (i, [vp, i]),
         "lbm_batch_set_time_blocking": (i, [vp, i]),
         "lbm_batch_set_time_blocking_for": (i, [vp, i, i]),
         "lbm_batch_set_wavefront_sites": (i, [vp, i, ll]),
@@ -360,6 +362,10 @@ class Solver:
     def set_time_blocking(self, steps_per_launch: int):
         self._check(self.lib.lbm_set_time_blocking(self.h, int(steps_per_launch)))
 
+    def set_launch_auto(self):
+        """The launch shape back to the library (lbm_set_launch_auto)."""
+        self._check(self.lib.lbm_set_launch_auto(self.h))
+
     def plain_launch(self) -> dict:
         """What plain steps run through at present: steps of a full launch, kernel
         ("tile", "wavefront", "square" or "single"), its rows, threads per
@@ -548,6 +554,11 @@ class Batch:
         rule (the lattices a single solver steps through the wavefront)."""
         self._check(self.lib.lbm_batch_set_wavefront_sites(self.h, PRECISIONS[precision],
                                                            int(min_sites)))
+
+    def set_launch_auto(self, precision: str):
+        """A storage type's launch shape back to the library
+        (lbm_batch_set_launch_auto)."""
+        self._check(self.lib.lbm_batch_set_launch_auto(self.h, PRECISIONS[precision]))
 
     def plain_launch(self, precision: str) -> dict:
         """What plain steps of a storage type run through at present; see

@@ -88,3 +88,74 @@ def test_solver_candidates_include_the_default_wavefront():
     assert autotune.solver_candidates(s, "fp32") == autotune.candidates(
         512, 0, 512, wavefront=True, precision="fp32")
     s.close()
+
+
+def test_tuner_times_the_library_choice_and_gives_it_back(monkeypatch, tmp_path):
+    """The library's own choice is among the timed shapes of single lattices,
+    in place and in batches, at its own depth; when it is the fastest it is what
+    runs afterwards, also from the cache and after other shapes."""
+    from paper_2208_14870_amd import autotune, lbm
+    need_gpu()
+    c = P.single_1024(0.3, 1, 1, n=128)
+
+    def solver(nx, prec, inplace=False):
+        s = lbm.Solver(nx, nx, prec, inplace=inplace)
+        if nx == 128:
+            s.set_material(c.material.lame_lambda, c.material.lame_mu)
+            s.set_body_force(dev(c.gx), dev(c.gy))
+        return s
+
+    seen = []
+
+    def auto_wins(set_shape, step, shapes, sites, **kw):
+        out = []
+        for shp in shapes:
+            try:
+                depth = set_shape(shp)
+            except lbm.LbmError:
+                continue
+            seen.append((shp, depth))
+            out.append((0.5 if shp == autotune.AUTO else 1.0, shp))
+        return sorted(out)
+
+    monkeypatch.setattr(autotune, "time_shapes", auto_wins)
+    for nx, prec, inplace in ((128, "fp64", False), (1024, "fp32", False), (600, "fp64", False),
+                              (1001, "fp32", True)):
+        s = solver(nx, prec, inplace)
+        want = s.plain_launch()
+        say(f"tuner {prec} {nx}^2 in place {inplace}: {want}")
+        seen.clear()
+        cache = str(tmp_path / f"{nx}{inplace}.json")
+        assert autotune.tune_solver(s, prec, cache_path=cache) == autotune.AUTO
+        assert (autotune.AUTO, want["steps_per_launch"]) in seen and len(seen) > 4
+        assert s.plain_launch() == want
+        s.set_time_blocking(1)
+        assert s.plain_launch() != want
+        assert autotune.tune_solver(s, prec, cache_path=cache) == autotune.AUTO
+        assert s.plain_launch() == want
+        s.close()
+    b = lbm.Batch(40, 1 << 30)
+    for k in range(34):
+        g = dev(np.zeros((100, 98)))
+        b.add(98, 100, 0.4, 0.3, g, g, "fp64")
+    want = b.plain_launch("fp64")
+    assert want["kernel"] == "wavefront" and want["steps_per_launch"] == 12
+    seen.clear()
+    assert autotune.tune_batch(b, "fp64", 34 * 9800, cache_path=None) == autotune.AUTO
+    assert (autotune.AUTO, 12) in seen and b.plain_launch("fp64") == want
+    b.close()
+
+
+def test_a_tuned_solver_is_not_slower_than_an_untouched_one():
+    """Where the library's own choice beats every shape that can be set (FP64
+    240 x 240: the small-lattice kernel), it is what the tuner keeps."""
+    from paper_2208_14870_amd import autotune, lbm
+    need_gpu()
+    s = lbm.Solver(240, 240, "fp64")
+    c = P.single_1024(0.3, 1, 1, n=240)
+    s.set_material(c.material.lame_lambda, c.material.lame_mu)
+    s.set_body_force(dev(c.gx), dev(c.gy))
+    assert s.plain_launch()["kernel"] == "square"
+    assert autotune.tune_solver(s, "fp64", cache_path=None) == autotune.AUTO
+    assert s.plain_launch()["kernel"] == "square"
+    s.close()
