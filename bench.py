@@ -28,7 +28,7 @@ Also reported on the same JSON line:
   large_8192    -- 8192 x 8192 FP64 / FP32 / scaled-FP16 step throughput (the
                    working set exceeds the 256 MB last-level cache) and the
                    reduced-precision displacement error on a 256^2 downsample;
-  batch         -- 512 uneven lattices in one launch per step; solves/s;
+  batch         -- 512 uneven lattices stepped together; solves/s;
   serving       -- Poisson arrivals, continuous batching, p50/p99 latency;
   cpu_baseline  -- the FP64 CPU oracle on a bounded sample of the workload.
 Inputs are seeded and synthetic (no dataset is involved).
@@ -49,8 +49,12 @@ PEAK_HBM_GBS = 8000.0
 BYTES_PER_SITE = {"fp64": 144, "fp32": 72, "fp16": 40}  # 8 pops in + 8 out + 2 force
 # VALU issue rate of MI355X in lane-instructions per second: 256 compute units x
 # 4 SIMDs, each issuing a wave64 VALU instruction over 4 cycles on 16 lanes, at
-# 2.4 GHz (packed FP32 is not used)
+# 2.4 GHz (packed FP32 is not used).  FP64 instructions and FP32 multiply-adds
+# issue at that rate (measured 4.4 clocks each), FP32 additions from two waves per
+# SIMD in half the clocks (2.2), so kernels in FP32 arithmetic are priced at twice
+# the rate, which none of their mixes can exceed.
 PEAK_VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
+VALU_RATE = {"fp64": 1, "fp32": 2, "fp16": 2}
 
 
 # the headers that define each fused kernel family
@@ -118,7 +122,7 @@ def roofline(prec, sites, avg_launch_us, steps_per_launch, kernel, counters=None
             out["traffic_over_min"] = round(tr / min_bytes, 3)
         valu = rec.get("valu_insts_per_launch")
         if valu:
-            out["valu_frac"] = round(64 * valu / t / PEAK_VALU_LANE_OPS, 4)
+            out["valu_frac"] = round(64 * valu / t / (VALU_RATE[prec] * PEAK_VALU_LANE_OPS), 4)
             out["valu_lane_insts_per_update"] = round(64 * valu / (sites * steps_per_launch), 2)
         out["counters"] = "profiles/" + counters + ".json"
     if note:

@@ -39,3 +39,18 @@ def test_roofline_arithmetic():
     assert abs(rf["effective_gbs"] - 8 * want) < 1.0
     assert rf["traffic"] is None and rf["valu_frac"] is None
     assert bench.PEAK_VALU_LANE_OPS == 256 * 4 * 16 * 2.4e9
+
+
+def test_valu_fraction_is_of_a_rate_that_can_be_reached(monkeypatch):
+    """Kernels in FP32 arithmetic issue additions in half the clocks of FP64
+    instructions: 8192^2 FP16 (590.9 M wave instructions in 930 us) is 0.52 of that
+    rate, not above 1; FP64 is priced at the full-width rate."""
+    sys.path.insert(0, ROOT)
+    import bench
+    rec = {"traffic_bytes_per_launch": 3.05e9, "valu_insts_per_launch": 590910224.0}
+    monkeypatch.setattr(bench, "measured_counters", lambda name, kernel=None: rec)
+    want = 64 * 590910224.0 / 930e-6 / (256 * 4 * 16 * 2.4e9)
+    for prec, f in (("fp16", 2), ("fp32", 2), ("fp64", 1)):
+        rf = bench.roofline(prec, 8192 ** 2, 930.0, 8, "k_wave<__half, 8, 1> (wavefront)", "x")
+        assert abs(rf["valu_frac"] - want / f) < 1e-3
+    assert want > 1 > want / 2
