@@ -503,9 +503,8 @@ static size_t workspace_bytes(int nx, int ny, int precision, bool polish, bool i
     if (nx < 1 || ny < 1 || !valid_prec(precision)) return 0;
     const long long N = (long long)nx * ny;
     const long long mi = max_items(nx, ny);
-    size_t b = al(sizeof(SlotDesc)) + 4 * al(sizeof(int)) + al(4 * 8) + al(sizeof(RiseGuard)) +
-               al(mi * sizeof(Item)) +
-               al(mi * 3 * 8) + al((kErrBlocks * 8 + 16) * 8);
+    size_t b = al(sizeof(SlotDesc)) + 3 * al(sizeof(int)) + al(sizeof(RiseGuard)) +
+               al(mi * sizeof(Item)) + al(mi * 3 * 8) + al((kErrBlocks * 8 + 16) * 8);
     b += lattice_bytes(N, precision, polish, inplace);
     return b;
 }
@@ -561,6 +560,7 @@ static int create_solver(int nx, int ny, int precision, int with_polish, bool in
     if (e != hipSuccess) {
         g_create_error = std::string("lbm_create: ") + hipGetErrorString(e);
         if (s->cap) (void)hipStreamDestroy(s->cap);
+        if (s->h_result) (void)hipHostFree(s->h_result);
         delete s;
         return LBM_E_HIP;
     }
@@ -590,8 +590,6 @@ static int create_solver(int nx, int ny, int precision, int with_polish, bool in
     s->d_range = reinterpret_cast<int*>(take(2 * sizeof(int)));
     s->d_first = reinterpret_cast<int*>(take(sizeof(int)));
     s->d_count = reinterpret_cast<int*>(take(sizeof(int)));
-    take(sizeof(int));
-    take(4 * 8);
     s->d_guard = reinterpret_cast<RiseGuard*>(take(sizeof(RiseGuard)));
     s->d_items = reinterpret_cast<Item*>(take(s->max_items_ * sizeof(Item)));
     s->d_partial = reinterpret_cast<double*>(take(s->max_items_ * 3 * 8));

@@ -224,10 +224,12 @@ __device__ __forceinline__ void bared_u(const C f[8], C gx, C gy, C& ux, C& uy) 
     uy = ((f[1] - f[3]) + (p + q)) + C(0.5) * gy;
 }
 
-// The collision with the force given as its quarter (qgx = gx/4, an exact
-// product): the half force that the first moments need is 2 qgx, taken inside
-// a fused multiply-add whose product is exact, so ux rounds as m10 + gx/2
-// does.  Kernels keep one value per force component and site instead of two.
+// The collision with the force given as its quarter, qgx = gx/4: the half force
+// that the first moments need is 2 qgx, taken inside a fused multiply-add, so ux
+// rounds as m10 + gx/2 does wherever the quarter is exact.  (It is not where it is
+// subnormal, forces below 2^-124 in FP32 and 2^-1020 in FP64: u then misses up to a
+// half of the smallest subnormal that bared_u's half force still holds.)  Kernels
+// keep one value per force component and site instead of two.
 template <typename C, bool GENERAL>
 __device__ __forceinline__ void collide_q(C f[8], C qgx, C qgy, const Coef<C>& k, C& ux, C& uy) {
 #pragma clang fp contract(off)

@@ -79,9 +79,9 @@ static __global__ __launch_bounds__(kBlock) void k_get_f(SlotDesc d, int sel, in
     for (int q = 0; q < 8; ++q) out[q * N + s] = (double)f[q] * d.inv_scale;
 }
 
-// Load a state f(n) given in the paper's order.  kLayPull and kLaySwapped
-// store f*(n-1)(x) = f(n)(x + c_q) (the inverse of the gather), in plane q or
-// plane opp(q); kLayNatural stores f(n) itself.
+// Load a state f(n) given in the paper's order into an in-place field: kLaySwapped
+// stores f*(n-1)(x) = f(n)(x + c_q) (the inverse of the gather) in plane opp(q),
+// kLayNatural f(n) itself.  (Two buffers: k_set_f_sums.)
 template <typename S>
 static __global__ __launch_bounds__(kBlock) void k_set_f(SlotDesc d, int sel, int layout,
                                                          const double* in, double scale) {
@@ -94,21 +94,13 @@ static __global__ __launch_bounds__(kBlock) void k_set_f(SlotDesc d, int sel, in
     const long long N = (long long)d.nx * d.ny;  // external layout [8][ny][nx]
     const int cx[8] = {1, 0, -1, 0, 1, -1, -1, 1};
     const int cy[8] = {0, 1, 0, -1, 1, 1, -1, -1};
+    const bool nat = layout == kLayNatural;
     for (int q = 0; q < 8; ++q) {
-        const bool nat = layout == kLayNatural;
         const int xs = nat ? x : (cx[q] > 0 ? xp : (cx[q] < 0 ? xm : x));
         const int ys = nat ? y : (cy[q] > 0 ? yp : (cy[q] < 0 ? ym : y));
         const double v = in[q * N + (long long)ys * d.nx + xs] * scale;
-        const int plane_q = layout == kLaySwapped ? opp(q) : q;
-        Store<S>::st(dst + plane_q * d.plane + s, (typename Store<S>::C)v);
+        Store<S>::st(dst + (nat ? q : opp(q)) * d.plane + s, (typename Store<S>::C)v);
     }
-}
-
-// Convert an FP64 array to the arithmetic type (force upload).
-template <typename C>
-static __global__ __launch_bounds__(kBlock) void k_convert(const double* in, C* out, long long n) {
-    const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) out[i] = (C)in[i];
 }
 
 // out = in * factor elementwise, between storage types (promotion for the
@@ -453,9 +445,9 @@ static __global__ __launch_bounds__(kBlock) void k_neutral_sums(SlotDesc d, int 
         }
 }
 
-// k_set_f into a buffer in kLayPull and k_neutral_sums of what it stores, in one
-// pass (the same sums in the same order; 2048 x 1500 FP32: the second pass over
-// the stored field took 28 us of 78).
+// Load a state f(n) given in the paper's order into a buffer in kLayPull, and
+// k_neutral_sums of what is stored, in one pass (the same sums in the same order;
+// 2048 x 1500 FP32: the second pass over the stored field took 28 us of 78).
 template <typename S>
 static __global__ __launch_bounds__(kBlock) void k_set_f_sums(SlotDesc d, int sel, const double* in,
                                                               double scale, double* partial) {
