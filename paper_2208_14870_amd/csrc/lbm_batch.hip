@@ -788,6 +788,7 @@ int lbm_batch_step(lbm_batch* b, long long nsteps, int check) {
             key.push_back(b->grid_for(p));
             key.push_back(b->grid_tile_for(p));
             key.push_back(b->grid_wave_for(p));
+            key.push_back(b->wave_v[p]);
         }
         auto it = b->graphs.find(key);
         if (it == b->graphs.end()) {

@@ -305,3 +305,39 @@ def test_batch_of_equal_lattices_takes_the_shape_that_fits(prec, nx, ny, count, 
             np.testing.assert_array_equal(got[0], want[0])
             np.testing.assert_array_equal(got[1], want[1])
     b.close()
+
+
+def test_replayed_steps_follow_a_change_of_the_lists_shape():
+    """Beside a storage type at one step per launch, steps replay captured graphs;
+    a list whose strips change from one wave to two at the same depth and grid
+    size captures its own.  The lattices that joined equal solo single steps."""
+    from paper_2208_14870_amd import lbm
+    need_gpu()
+    say("batch: the list's shape changes between replays")
+    mat = P.Material.from_shear_poisson(0.9, 0.3)
+    b = lbm.Batch(32, GIB)
+    b.set_time_blocking(1, "fp64")
+    b.set_wavefront_sites("fp32", 0)
+    g0 = [dev(a) for a in _load(8, 8, 1)]
+    b.add(8, 8, mat.lame_lambda, mat.lame_mu, *g0, "fp64")
+
+    def add(sizes):
+        out = []
+        for k, (nx, ny) in enumerate(sizes):
+            load = _load(nx, ny, 500 + k)
+            out.append((nx, ny, load, b.add(nx, ny, mat.lame_lambda, mat.lame_mu,
+                                            *(dev(a) for a in load), "fp32")))
+        return out
+
+    for sizes, threads in (([(30, 16)] * 12, 256), ([(98, 16)] * 6 + [(30, 16)] * 4, 512)):
+        lattices = add(sizes)
+        got = b.plain_launch("fp32")
+        assert (got["steps_per_launch"], got["threads"]) == (12, threads), got
+        b.step(24)
+        for nx, ny, load, slot in (lattices[0], lattices[-1]):
+            want = _solo(nx, ny, "fp32", mat, *load, 24)
+            for t, w in zip(b.displacement(slot), want):
+                np.testing.assert_array_equal(host(t), w)
+        for *_, slot in lattices:
+            b.remove(slot)
+    b.close()
