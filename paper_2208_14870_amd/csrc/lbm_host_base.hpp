@@ -1,5 +1,6 @@
 // Host-side basics shared by every translation unit: alignment and element
-// sizes, the wavefront's halo sizes, and the wavefront launchers (compiled in translation units of their own).
+// sizes, the wavefront's halo sizes, and the wavefront launchers (compiled in
+// translation units of their own).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,10 +28,10 @@ inline size_t arith_bytes(int prec) { return prec == LBM_FP64 ? 8 : 4; }
 inline bool valid_prec(int p) { return p == LBM_FP64 || p == LBM_FP32 || p == LBM_FP16; }
 
 // Wavefront launch of `ns` plain steps (2..8, or 12 for FP64 and FP32) on slot 0
-// (single lattice), segments of hs rows; v: columns per lane (2 needs an even nx
-// and non-FP64 storage; half storage with two columns runs at most four steps);
-// sr: half storage with stochastic rounding; gen: free relaxation rates (not
-// with sr).  Defined in lbm_wave.hip and lbm_wave_general.hip.
+// (single lattice), segments of hs rows; v: the strips' shape (lbm_wave_shape.hpp;
+// 2 needs an even nx and non-FP64 storage, and runs at most four steps of half
+// storage); sr: half storage with stochastic rounding; gen: free relaxation rates
+// (not with sr).  Defined in lbm_wave.hip and lbm_wave_general.hip.
 hipError_t launch_wave(int prec, int ns, int v, int nx, int ny, int hs, const SlotDesc* slots,
                        int flip, hipStream_t st, bool sr = false, bool gen = false);
 hipError_t launch_wave_general(int prec, int ns, int v, unsigned grid, hipStream_t st,
@@ -97,12 +98,12 @@ inline size_t wave_halo_bytes(int prec, int ns, int v, int nx, int ny, int hs) {
            al((size_t)(8 * segs * 2LL * ns * nx) * elem_bytes(prec));
 }
 
-// Wavefront over a list of workgroups of several lattices (a batch; two
-// buffers, one column per lane, any widths): the launch runs items[wrange[0] ..
-// wrange[1] - 1] (wrange in device memory), each naming its lattice's
-// descriptor slot, strip (as wide as the output of the list's depth ns' >= ns:
-// a shallower launch leaves the surplus strips idle) and rows.  nitems: the
-// list's current length, to check the grid.  Defined in lbm_wave_batch.hip.
+// Wavefront over a list of workgroups of several lattices (a batch; two buffers,
+// one column per lane: v 0 or 1, any widths): the launch runs items[wrange[0] ..
+// wrange[1] - 1] (wrange in device memory), each naming its lattice's descriptor
+// slot, strip (as wide as the output of the list's shape and depth ns' >= ns: a
+// shallower launch leaves the surplus strips idle) and rows.  nitems: the list's
+// current length, to check the grid.  Defined in lbm_wave_batch.hip.
 hipError_t launch_wave_list(int prec, int ns, int v, const SlotDesc* slots, const WaveItem* items,
                             const int* wrange, int nitems, int flip, unsigned grid,
                             hipStream_t st);

@@ -1,5 +1,5 @@
 // Wavefront launches with two buffers (k_wave): the instantiations for every
-// storage type, depth and lane width, in a translation unit of their own so
+// storage type, depth and strip shape, in a translation unit of their own so
 // that they compile beside the rest of the library.
 #include <hip/hip_runtime.h>
 

@@ -103,6 +103,7 @@ template <> struct VecIO<__half, 2> {
     }
 };
 
+// VS: the shape's code (lbm_wave_shape.hpp).
 template <typename S, int NS, int VS>
 struct WaveShape {
     static constexpr int V = wave_lane_cols(VS);  // columns per lane
@@ -243,7 +244,8 @@ __device__ __forceinline__ void wave_group(const WaveLaunch& L, const SlotDesc& 
                                            int sy, int ya, int yb) {
     using C = typename Store<S>::C;
     using Sh = WaveShape<S, NS, VS>;
-    constexpr int V = Sh::V, R = Sh::R, W = Sh::W, TC = Sh::TC, NG = Sh::NG, XW = Sh::XW, PF = GEN ? 1 : Sh::PF;
+    constexpr int V = Sh::V, R = Sh::R, W = Sh::W, TC = Sh::TC, NG = Sh::NG, XW = Sh::XW,
+                  PF = GEN ? 1 : Sh::PF;
     constexpr bool kSR = SR && std::is_same<S, __half>::value;
     constexpr bool kNat = IP && (NS % 2 == 1);      // level 0 is f(n) itself
     constexpr int NL = LAST ? NS - Sh::before(NG - 1) : Sh::LPW;  // levels of this group
@@ -505,7 +507,8 @@ __device__ __forceinline__ void wave_group(const WaveLaunch& L, const SlotDesc& 
 template <typename S, int NS, int VS, bool SR = false, bool IP = false, bool LIST = false,
           bool GEN = false>
 static __global__ __launch_bounds__((WaveShape<S, NS, VS>::NT))
-__attribute__((amdgpu_waves_per_eu(WaveShape<S, NS, VS>::WPE - (GEN && WaveShape<S, NS, VS>::WPE > 2)))) void k_wave(WaveLaunch L) {
+__attribute__((amdgpu_waves_per_eu(
+    WaveShape<S, NS, VS>::WPE - (GEN && WaveShape<S, NS, VS>::WPE > 2)))) void k_wave(WaveLaunch L) {
     using C = typename Store<S>::C;
     using Sh = WaveShape<S, NS, VS>;
     static_assert(!(SR && IP), "no stochastic rounding in place");

@@ -1,6 +1,7 @@
 // Wavefront launches over a list of workgroups of several lattices (the
 // lattices on a batch's wavefront list): k_wave<..., LIST> with one column per
-// lane for every storage type and depth, in a translation unit of its own.
+// lane, in strips of two waves or one, for every storage type and depth, in a
+// translation unit of its own.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

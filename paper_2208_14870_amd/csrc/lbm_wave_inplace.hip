@@ -1,6 +1,5 @@
-// In-place register-wavefront launches (one population buffer): the halo
-// copy (k_wave_halo) and k_wave<..., IP> for every storage type, depth and
-// lane width, in a translation unit of their own.
+// In-place wavefront launches (one population buffer): the halo copy
+// (k_wave_halo) and k_wave<..., IP> for every storage type, depth and strip shape, in a translation unit of their own.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
