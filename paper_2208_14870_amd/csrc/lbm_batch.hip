@@ -164,6 +164,15 @@ struct lbm_batch {
     int range_tile_host[3][2] = {{0, 0}, {0, 0}, {0, 0}};
     int wrange_host[3][2] = {{0, 0}, {0, 0}, {0, 0}};
     std::vector<WaveItem> h_witems;
+    WaveItem* h_wstage = nullptr;  // pinned staging of h_witems (cap_wstage items)
+    size_t cap_wstage = 0;
+    struct SizeCount {
+        int nx, ny;
+        long long count;
+        long long sites() const { return (long long)nx * ny; }
+    };
+    std::vector<int> h_active[3];         // rebuild's scratch
+    std::vector<SizeCount> h_sizes[3];
     // launches per precision since the descriptors were written: lattices of one
     // storage type share a launch parity (buffer selector cur ^ (phase & 1));
     // each type runs its own steps per launch, so each keeps its own count
@@ -265,6 +274,26 @@ struct lbm_batch {
                 stats_pending[i] = 0;
             }
         }
+        // the active slots of each precision, and their sizes without repeats
+        // (an admission rebuilds the list, so a pass over every slot for each
+        // shape and height tried would be felt)
+        for (int p = 0; p < 3; ++p) h_active[p].clear(), h_sizes[p].clear();
+        for (int i = 0; i < max_slots; ++i)
+            if (slots[i].active) h_active[slots[i].L.prec].push_back(i);
+        for (int p = 0; p < 3; ++p) {
+            for (int i : h_active[p]) h_sizes[p].push_back({slots[i].L.nx, slots[i].L.ny, 1});
+            std::sort(h_sizes[p].begin(), h_sizes[p].end(), [](const SizeCount& a, const SizeCount& b) {
+                return a.nx != b.nx ? a.nx < b.nx : a.ny < b.ny;
+            });
+            size_t n = 0;
+            for (const SizeCount& c : h_sizes[p]) {
+                if (n > 0 && h_sizes[p][n - 1].nx == c.nx && h_sizes[p][n - 1].ny == c.ny)
+                    ++h_sizes[p][n - 1].count;
+                else
+                    h_sizes[p][n++] = c;
+            }
+            h_sizes[p].resize(n);
+        }
         for (int p = 0; p < 3; ++p) {
             long long sites = 0;
             bool large = false, small = false;  // a lattice on / not on the wavefront list
@@ -272,24 +301,21 @@ struct lbm_batch {
             // its lattices on the list (or all of them) through a shape of the wavefront
             auto total = [&](bool all, int v, int ns) {
                 double t = 0.0;
-                for (const BSlot& s : slots)
-                    if (s.active && s.L.prec == p && (all || on_wave_list(p, s.L.N)))
-                        t += wave_cost(p, v, ns, s.L.nx, s.L.ny);
+                for (const SizeCount& c : h_sizes[p])
+                    if (all || on_wave_list(p, c.sites())) t += c.count * wave_cost(p, v, ns, c.nx, c.ny);
                 return t;
             };
-            for (const BSlot& s : slots)
-                if (s.active && s.L.prec == p) {
-                    sites += s.L.N;
-                    tiles += tile_cost(p, s.L.nx, s.L.ny);
-                }
+            for (const SizeCount& c : h_sizes[p]) {
+                sites += c.count * c.sites();
+                tiles += c.count * tile_cost(p, c.nx, c.ny);
+            }
             wave_all[p] = false;
             if (sites >= batch_wave_total(p) && wave_min[p] < 0) {
                 int v, ns;
                 wave_best_shape(p, [&](int a, int b) { return total(true, a, b); }, v, ns);
                 wave_all[p] = wave_over_tile(total(true, v, ns), tiles);
             }
-            for (const BSlot& s : slots)
-                if (s.active && s.L.prec == p) (on_wave_list(p, s.L.N) ? large : small) = true;
+            for (const SizeCount& c : h_sizes[p]) (on_wave_list(p, c.sites()) ? large : small) = true;
             // the wavefront runs its own depth best, and its lattices carry the
             // work; beside lattices on the tile kernel the eight steps that both run
             auto listed = [&](int v, int ns) { return total(false, v, ns); };
@@ -302,7 +328,7 @@ struct lbm_batch {
         // Per precision: the tile work list of every lattice (single steps and
         // residual checks), the lattices the tile kernel steps in plain fused
         // launches first; the lattices of the wavefront list (on_wave_list)
-        // take those launches through it instead, one item per wave.
+        // take those launches through it instead, one item per workgroup.
         h_witems.clear();
         for (int p = 0; p < 3; ++p) {
             range_host[p][0] = (int)total;
@@ -310,9 +336,8 @@ struct lbm_batch {
             int wave_ny = 0;  // rows of its tallest wavefront lattice
             const int w = tb[p] >= 2 ? wave_out(tb[p], wave_v[p], is_half(p)) : 0;
             for (int pass = 0; pass < 2; ++pass) {
-                for (int i = 0; i < max_slots; ++i) {
+                for (int i : h_active[p]) {
                     BSlot& s = slots[i];
-                    if (!s.active || s.L.prec != p) continue;
                     s.wave = w > 0 && on_wave_list(p, s.L.N);
                     if (s.wave != (pass == 1)) continue;
                     s.L.bx_log2 = bx_log2;
@@ -333,19 +358,20 @@ struct lbm_batch {
             range_host[p][1] = (int)total;
             auto groups = [&](int hs) {
                 long long n = 0;
-                for (const BSlot& s : slots)
-                    if (s.active && s.L.prec == p && s.wave)
-                        n += (long long)((s.L.nx + w - 1) / w) * ((s.L.ny + hs - 1) / hs);
+                for (const SizeCount& c : h_sizes[p])
+                    if (on_wave_list(p, c.sites()))
+                        n += c.count * ((c.nx + w - 1) / w) * ((c.ny + hs - 1) / hs);
                 return n;
             };
-            const int hs = wave_ny ? wave_segment_rows(tb[p], cus, wave_blocks_per_cu(p, tb[p], wave_v[p]),
-                                                       16, wave_ny, groups)
-                                   : 1;
+            const int hs =
+                wave_ny ? wave_segment_rows(tb[p], cus, wave_blocks_per_cu(p, tb[p], wave_v[p]), 16,
+                                            wave_ny, groups)
+                        : 1;
             // segments of equal height per lattice, the longest first: the last
             // round of workgroups then ends with short ones
-            for (int i = 0; i < max_slots && w > 0; ++i) {
+            for (int i : h_active[p]) {
                 const BSlot& s = slots[i];
-                if (!s.active || s.L.prec != p || !s.wave) continue;
+                if (!s.wave) continue;
                 const int strips = (s.L.nx + w - 1) / w, segs = (s.L.ny + hs - 1) / hs;
                 const int rows = (s.L.ny + segs - 1) / segs;
                 for (int ya = 0; ya < s.L.ny; ya += rows)
@@ -382,9 +408,24 @@ struct lbm_batch {
             e = hipMemcpyAsync(d_range_tile, rng + 6, 6 * sizeof(int), hipMemcpyHostToDevice, stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(d_wrange, rng + 12, 6 * sizeof(int), hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess && !h_witems.empty())
-            e = hipMemcpy(d_witems, h_witems.data(), h_witems.size() * sizeof(WaveItem),
-                          hipMemcpyHostToDevice);
+        if (e == hipSuccess && !h_witems.empty()) {
+            // through pinned staging, grown as needed (free: the stream was
+            // synchronised above; a copy from pageable memory is 13 us longer)
+            const size_t n = h_witems.size();
+            if (n > cap_wstage) {
+                if (h_wstage) (void)hipHostFree(h_wstage);
+                h_wstage = nullptr;
+                cap_wstage = 0;
+                e = hipHostMalloc(reinterpret_cast<void**>(&h_wstage), 2 * n * sizeof(WaveItem),
+                                  hipHostMallocDefault);
+                if (e == hipSuccess) cap_wstage = 2 * n;
+            }
+            if (e == hipSuccess) {
+                std::memcpy(h_wstage, h_witems.data(), n * sizeof(WaveItem));
+                e = hipMemcpyAsync(d_witems, h_wstage, n * sizeof(WaveItem), hipMemcpyHostToDevice,
+                                   stream);
+            }
+        }
         if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "rebuild");
         // descriptors of the active slots: one copy from pinned staging (the
@@ -605,6 +646,7 @@ int lbm_batch_destroy(lbm_batch* b) {
     if (!b) return LBM_E_ARG;
     (void)hipStreamSynchronize(b->stream);
     b->drop_graphs();
+    if (b->h_wstage) (void)hipHostFree(b->h_wstage);
     if (b->cap) (void)hipStreamDestroy(b->cap);
     if (b->h_rows) (void)hipHostFree(b->h_rows);
     if (b->h_result) (void)hipHostFree(b->h_result);
