@@ -174,3 +174,60 @@ def test_general_rates_at_a_chosen_depth_on_small_lattices(prec, nx, ny):
             p = s.plain_launch()
             assert (p["kernel"], p["steps_per_launch"]) == ("square", depth), p
         _same(nx, ny, prec, (depth, 2 * depth + depth // 2, 3), shape, rates=RATES)
+
+
+@pytest.mark.parametrize("prec,nx,ny,rates", [
+    ("fp64", 200000, 1, None), ("fp32", 400001, 1, None), ("fp64", 7, 30000, RATES),
+    ("fp32", 5, 40000, RATES), ("fp64", 60000, 3, RATES), ("fp16", 19, 20000, RATES)])
+def test_thin_lattices_run_single_steps(prec, nx, ny, rates):
+    """One row, and with free rates few columns or rows: one step per launch by
+    default, checks included, in every length of call."""
+    from paper_2208_14870_amd import lbm
+
+    def shape(s):
+        assert s.plain_launch()["kernel"] == "single", s.plain_launch()
+    _same(nx, ny, prec, (1, 2, 5, 70), shape, rates=rates)
+    s = lbm.Solver(nx, ny, prec)
+    s.set_material(0.4, 0.3)
+    g = dev(np.random.default_rng(1).standard_normal((ny, nx)) * 1e-3)
+    s.set_body_force(g, g)
+    r = []
+    for one in (False, True):
+        s.reset()
+        if one:
+            s.set_time_blocking(1)
+        r.append([s.step_checked(n) for n in (2, 9, 70)] + [s.solve_to_tol(0.0, 20, 7)[1]])
+    np.testing.assert_allclose(r[0], r[1], rtol=nx * ny * 2.0 ** -52, atol=0)
+    s.close()
+
+
+def test_half_storage_stays_with_tiles_that_cost_less():
+    """A 64-column FP16 lattice of 2^24 sites and more, whose nominal kernel is the
+    wavefront: its tiles cost less, and run it; states equal single steps."""
+    from paper_2208_14870_amd import lbm
+    import torch
+    need_gpu()
+    nx, ny = 64, 262200
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    f = torch.randn(2, ny, nx, generator=g, device="cuda", dtype=torch.float64) * 1e-4
+    f -= f.mean(dim=(1, 2), keepdim=True)
+    out = []
+    for one in (False, True):
+        s = lbm.Solver(nx, ny, "fp16")
+        s.set_material(0.4, 0.3)
+        s.set_body_force(f[0].contiguous(), f[1].contiguous())
+        p = s.plain_launch()
+        assert s.launch_config()["kernel"] == "wavefront"
+        assert (p["kernel"], p["steps_per_launch"]) == ("tile", 8), p
+        if one:
+            s.set_time_blocking(1)
+        for n in (8, 3, 13):
+            s.step(n)
+        r = s.step_checked(10)
+        out.append((r, s.displacement()))
+        s.close()
+        del s
+    for a, b in zip(out[0][1], out[1][1]):
+        assert torch.equal(a, b)
+    assert out[0][0] == pytest.approx(out[1][0], rel=nx * ny * 2.0 ** -52)
