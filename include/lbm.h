@@ -347,22 +347,42 @@ int lbm_set_tile(lbm_solver *s, int bx_log2, int rows_per_thread, int blocks_per
 /* Temporal blocking: with steps_per_launch = k in 2..8, plain steps run k at a
  * time through one fused kernel, so populations cross HBM once per k steps.
  * Results are identical to single steps.  A residual check rides on a fused
- * tile launch.  General rates run through the wavefront (two buffers, without
- * stochastic rounding; one step per launch otherwise).  Overrides the tile
- * shape of lbm_set_tile while active.  While neither this nor
- * lbm_set_fused_kernel nor lbm_set_tile_rows has been called, the lattices
- * whose default is the wavefront, and general rates, run at the library's own
- * depth (twelve steps per launch for FP64 and FP32, eight for FP16) and
- * segment height.  Default by storage type and size: FP32 and FP16
- * 8 above 2^17 sites, else 4; FP64 5 below 458752 sites (the tile kernel),
- * else 8 (the wavefront; also after a polish switch).  The fused kernel follows the default of
- * lbm_set_fused_kernel for k until the caller picks one.  In place: the
+ * tile launch, or on one of the small-lattice kernel.  Overrides the tile shape
+ * of lbm_set_tile while active.
+ *
+ * While neither this nor lbm_set_fused_kernel nor lbm_set_tile_rows has been
+ * called, the library chooses the kernel, the depth and the segment height of
+ * plain steps (lbm_get_plain_launch says which), two buffers:
+ *  - lattices of no more 32 x 32 regions than compute units at four steps (up to
+ *    about 173000 sites): the small-lattice kernel at four to twelve steps;
+ *  - one row, or with general rates less than 4 rows or 8 columns (FP16 20
+ *    columns): one step per launch;
+ *  - FP64 from 150000 sites, FP32 from 327680, FP16 from 2^20 (with stochastic
+ *    rounding 2^21), and general rates: the wavefront at twelve steps (FP64 and
+ *    FP32; eight where that suits a narrow width better, and for FP16), except
+ *    where an estimate for the lattice's width and height favours the tile kernel
+ *    (FP16 of any shape, FP64 of fewer than 8 rows);
+ *  - the tile kernel between, at the nominal depth.
+ * A remainder, or a check, of a few steps of a wavefront lattice may run through
+ * the tile kernel.
+ *
+ * Nominal depth (the tile kernel's, and what lbm_get_launch_config reports): FP32
+ * and FP16 8 above 2^17 sites, else 4; FP64 5 below 458752 sites (the tile
+ * kernel), else 8 (the wavefront; also after a polish switch).  The fused kernel
+ * of a chosen k follows the nominal default of lbm_set_fused_kernel until the
+ * caller picks one.  General rates at a chosen k: the small-lattice kernel where
+ * its regions at k steps are no more than the compute units, else the wavefront
+ * (one step per launch with stochastic rounding or a chosen tile kernel).
+ *
+ * In place: the
  * in-place wavefront (see lbm_create_inplace), one column per lane for FP64
- * and for FP16 above four steps, two otherwise on even widths; segments of
- * 256 rows, halved down to 32 while the lattice would give fewer than 4096
- * waves, until the caller picks a segment height.  Errors: LBM_E_ARG (k
- * outside 1..8), LBM_E_WORKSPACE (in place, k >= 2 and the halo room of the
- * workspace is too small for k). */
+ * and for FP16 above four steps, two otherwise on even widths; nominal segments
+ * of 256 rows, halved down to 32 while the lattice would give fewer than 4096
+ * waves.  Until the caller picks a segment height, longer segments run where they
+ * finish sooner, and twelve steps per launch instead of a default of eight (FP64,
+ * FP32) where their copies fit the halo room.  Errors: LBM_E_ARG (k outside
+ * 1..8), LBM_E_WORKSPACE (in place, k >= 2 and the halo room of the workspace is
+ * too small for k). */
 int lbm_set_time_blocking(lbm_solver *s, int steps_per_launch);
 
 /* Tile height of the LDS tile kernel (the tile is 64 columns wide): rows in
@@ -381,7 +401,8 @@ enum lbm_fused_kernel {
      * 16 above. */
     LBM_FUSED_TILE = 0,
     /* Wavefront: a workgroup owns a strip of columns (two waves side by side
-     * with one column per lane, or one wave with two per lane for FP32/FP16 on
+     * with one column per lane; one such wave where that leaves fewer columns of a
+     * narrow lattice idle; or one wave with two per lane for FP32/FP16 on
      * even widths) with a ring of k columns per side (with two per lane: 4 for
      * k <= 4, k rounded up to even above) and marches along y through segments
      * of `segment_rows` rows; its waves are a pipeline over the k steps, each
@@ -466,11 +487,12 @@ const char *lbm_last_error(const lbm_solver *s);
  * list of their (lattice, strip, segment) workgroups, one column per lane, beside
  * the tile launch of the others.  By default (see
  * lbm_batch_set_wavefront_sites) these are, per storage type, all of its
- * lattices once they hold at least 200000 (FP64), 300000 (FP32) or 2^21 (FP16)
- * sites together, and otherwise the large ones (FP32 from 2^20 sites, FP64 from
- * 458752, FP16 from 2^24).  A precision with lattices on the list defaults to
- * eight steps per launch.  Residual checks run through the tile kernel for every
- * lattice.  Results are identical either way (each equals single steps). */
+ * lattices once they hold at least 300000 (FP64), 700000 (FP32) or 2^21 (FP16)
+ * sites together and an estimate over their widths and heights says that the
+ * wavefront is clearly faster than the tiles, and otherwise the large ones (FP32
+ * from 2^20 sites, FP64 from 458752, FP16 from 2^24).  Residual checks run
+ * through the tile kernel for every lattice.  Results are identical either way
+ * (each equals single steps). */
 
 /* Bytes of arena one lattice occupies in a batch at `precision` (with
  * `with_polish`: plus its FP64 polish state).  Used for admission. */
@@ -512,7 +534,8 @@ int lbm_batch_remove(lbm_batch *b, int slot);
 /* Advance every active lattice by nsteps >= 1.  With check != 0 the last two
  * steps also evaluate each lattice's residual r(n) (as in lbm_solve_to_tol)
  * at its step count after the call; read them with lbm_batch_residuals.
- * Chunks are replayed from captured HIP graphs.  Asynchronous. */
+ * Launches are enqueued one by one, or replayed from a captured HIP graph
+ * where a storage type runs one step per launch.  Asynchronous. */
 int lbm_batch_step(lbm_batch *b, long long nsteps, int check);
 
 /* Blocking: residual of the last checked chunk and step count per slot,
@@ -558,9 +581,10 @@ int lbm_batch_set_launch_auto(lbm_batch *b, int precision);
 int lbm_batch_get_plain_launch(lbm_batch *b, int precision, int out[5]);
 
 /* Temporal blocking for all lattices of the batch (see lbm_set_time_blocking,
- * 1..8).  Until set, a storage type with lattices on the wavefront list runs
- * eight steps per launch (FP64 and FP32 twelve when all of its lattices are on
- * it), and otherwise takes the tile kernel's default for
+ * 1..8).  Until set, a storage type whose lattices are all on the wavefront list
+ * runs twelve steps per launch (FP64 and FP32; eight where that suits narrow
+ * lattices better, and for FP16), one with some of them on it eight, and one
+ * with none takes the tile kernel's default for
  * the total sites of its lattices in the batch (FP64 5, FP32 / FP16 8 above
  * 2^17 sites).  Errors: LBM_E_ARG. */
 int lbm_batch_set_time_blocking(lbm_batch *b, int steps_per_launch);

@@ -43,9 +43,9 @@ def candidates(nx: int, min_bx: int = 3, ny: int = 0, wavefront: bool = False,
     """The library's own choice (AUTO); single-step tile shapes; the fused LDS
     tile kernel at 2..8 steps with one workgroup per tile or a persistent grid,
     and for single FP32 lattices also its 24-row tile at five steps or more; and
-    (single lattices) the wavefront at 3..8 steps with a few segment heights.  In place: single-step
-    shapes and the in-place wavefront (those the solver's halo room admits are
-    timed); fused=False: single-step shapes only."""
+    (single lattices) the wavefront at 3..8 steps with a few segment heights.  In
+    place: single-step shapes and the in-place wavefront (those the solver's halo
+    room admits are timed); fused=False: single-step shapes only."""
     if inplace:
         out = [AUTO] if fused else []
         if fused:

@@ -3,9 +3,9 @@
 // walks a work list of (lattice, tile) items; per-lattice arithmetic is the
 // single-lattice kernel's, so a lattice gives the same populations alone
 // and in a batch.  Lattices live in a caller-owned device arena managed by a
-// first-fit allocator; chunks of steps are replayed from captured HIP graphs
-// whose kernel arguments (descriptor table, work list, per-precision item
-// ranges) stay valid while lattices join and leave.
+// first-fit allocator.  Fused launches are enqueued one by one; single steps are
+// replayed from captured HIP graphs whose kernel arguments (descriptor table,
+// work list, per-precision item ranges) stay valid while lattices join and leave.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -243,9 +243,9 @@ struct lbm_batch {
 
     int ensure() { return dirty ? rebuild() : LBM_OK; }
 
-    // Default rule: every lattice of the type once its lattices hold at least
-    // batch_wave_total sites together, else those a single solver steps
-    // through the wavefront.
+    // Default rule: every lattice of the type (wave_all) once its lattices hold at
+    // least batch_wave_total sites together and cost less there than through tiles
+    // (wave_over_tile), else the large ones (wave_by_default).
     bool on_wave_list(int p, long long sites) const {
         return wave_min[p] < 0 ? wave_all[p] || wave_by_default(p, sites) : sites >= wave_min[p];
     }
@@ -594,7 +594,9 @@ int lbm_batch_create(int max_slots, void* arena, size_t arena_bytes, void* strea
     b->d_rows = reinterpret_cast<SlotRow*>(take((max_slots + 5) * sizeof(SlotRow)));
     b->d_red = reinterpret_cast<double*>(take((kErrBlocks * 8 + 16) * sizeof(double)));
     b->d_items = reinterpret_cast<Item*>(take(b->cap_items * sizeof(Item)));
-    // wavefront items: no more than tile items (one covers at least 48 x 16 sites)
+    // wavefront items: no more than max_items per lattice, since the narrowest
+    // strip is 40 columns and the shortest nominal segment 16 rows: at most
+    // (nx / 40 + 1) (ny / 16 + 1) of them
     b->d_witems = reinterpret_cast<WaveItem*>(take(b->cap_items * sizeof(WaveItem)));
     b->d_partial = reinterpret_cast<double*>(take(b->cap_items * 3 * sizeof(double)));
     if (off > arena_bytes) {

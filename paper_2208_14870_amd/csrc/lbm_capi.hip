@@ -4,7 +4,7 @@
 // Scheme: Boolakee, Geier, De Lorenzis, arXiv 2208.14870 (Algorithm 1,
 // Table "scheme").  Every step of the method runs in the kernels of
 // lbm_device.hpp; this file owns handles, validation, memory layout inside
-// caller-owned workspaces, work lists, HIP graph capture of step chunks and
+// caller-owned workspaces, work lists, HIP graph capture of single steps and
 // the pseudo-time convergence loop.
 #include <hip/hip_runtime.h>
 
@@ -148,10 +148,12 @@ struct lbm_solver {
         }
     }
 
-    // The launches of plain steps.  Left to the library, large lattices and all
-    // lattices with free rates run through the wavefront at its own depth and
-    // segment height; a depth, kernel or height that the caller chose is taken
-    // as given (higher only where a launch would hold too many threads).
+    // The launches of plain steps.  Left to the library, lattices of few 32 x 32
+    // regions run through the small-lattice kernel (square_depth), thin ones one
+    // step per launch, larger ones (wave_auto) and otherwise all with free rates
+    // through the wavefront at its own depth and segment height; a depth, kernel or
+    // height that the caller chose is taken as given (higher only where a launch
+    // would hold too many threads).
     void make_plan() {
         plan = PlainPlan();
         L.single = false;

@@ -616,8 +616,8 @@ inline int wave_cols_deep(int prec, int nx, int ny) {
 // sites (FP32 1024^2: 232 against 149 GLUPS at four), four on smaller lattices
 // (FP32 256^2: 49 against 42).  FP64 (whose LDS tile is twice as large): five
 // through the tile kernel (1024^2: 106 against 98 GLUPS at four), eight where
-// the wavefront is the default (wave_by_default, single lattices; a
-// batch always runs tiles).
+// the wavefront is the nominal default (wave_by_default; tiles_only: a batch
+// with no lattice on its wavefront list).
 inline int default_time_blocking(int prec, long long sites, bool tiles_only = false) {
     if (prec == LBM_FP64) return (tiles_only || !wave_by_default(prec, sites)) ? 5 : 8;
     return sites > (1LL << 17) ? 8 : 4;
@@ -694,7 +694,7 @@ struct Lattice {
     double lam = 0, mu = 0;
     bool has_material = false, has_force = false;
     int e_scale = 0;  // half storage: stored = f * 2^-e
-    bool sr = false;       // half storage rounds stochastically (two buffers, no wavefront)
+    bool sr = false;       // half storage rounds stochastically (two buffers)
     unsigned sr_seed = 0;
     double gmax = 0;  // max |g| of the force (initial half scale)
     // The mean first moments of the exact trajectory: sum_x m10, sum_x m01 were

@@ -1,5 +1,6 @@
 // In-place wavefront launches (one population buffer): the halo copy
-// (k_wave_halo) and k_wave<..., IP> for every storage type, depth and strip shape, in a translation unit of their own.
+// (k_wave_halo) and k_wave<..., IP> for every storage type, depth and strip
+// shape, in a translation unit of their own.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -551,7 +551,8 @@ class Batch:
     def set_wavefront_sites(self, precision: str, min_sites: int):
         """Lattices of `precision` with at least `min_sites` sites (0: all) take
         their plain fused steps through the wavefront list; -1: the default
-        rule (the lattices a single solver steps through the wavefront)."""
+        rule (all lattices of the type once they are many enough and suit its
+        strips, else the large ones; see lbm_batch_set_wavefront_sites)."""
         self._check(self.lib.lbm_batch_set_wavefront_sites(self.h, PRECISIONS[precision],
                                                            int(min_sites)))
 
