@@ -222,9 +222,12 @@ struct lbm_batch {
         // power-of-two buckets keep captured graphs valid while the list changes
         unsigned g = 8;
         while (g < (unsigned)n) g <<= 1;
+        g = std::min(g, kMostGroups);  // its workgroups walk the list
         if (blocks_per_cu > 0) g = std::min(g, (unsigned)(cus * blocks_per_cu + 7) / 8 * 8);
         return g;
     }
+    // workgroups of up to 512 threads with fewer than 2^32 threads in a launch
+    static constexpr unsigned kMostGroups = (1u << 23) - 8;
     // every lattice of a precision (single steps, residual checks)
     unsigned grid_for(int prec) const { return bucket(range_host[prec][1] - range_host[prec][0]); }
     // the lattices the tile kernel steps in plain fused launches
@@ -237,7 +240,7 @@ struct lbm_batch {
         if (n <= 0) return 0;
         unsigned g = 8;
         while (g < (unsigned)n) g <<= 1;
-        return g;
+        return g <= kMostGroups ? g : (unsigned)(n + 7) / 8 * 8;
     }
 
 
