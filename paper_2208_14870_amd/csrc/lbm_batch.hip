@@ -226,8 +226,6 @@ struct lbm_batch {
         if (blocks_per_cu > 0) g = std::min(g, (unsigned)(cus * blocks_per_cu + 7) / 8 * 8);
         return g;
     }
-    // workgroups of up to 512 threads with fewer than 2^32 threads in a launch
-    static constexpr unsigned kMostGroups = (1u << 23) - 8;
     // every lattice of a precision (single steps, residual checks)
     unsigned grid_for(int prec) const { return bucket(range_host[prec][1] - range_host[prec][0]); }
     // the lattices the tile kernel steps in plain fused launches

@@ -254,7 +254,7 @@ struct lbm_solver {
         if (e != hipSuccess) return hip_fail(e, "descriptor upload");
         unsigned g = (unsigned)((nitems + 7) / 8 * 8);
         if (blocks_per_cu > 0) g = std::min(g, (unsigned)(cus * blocks_per_cu + 7) / 8 * 8);
-        grid = std::max(8u, g);
+        grid = std::min(std::max(8u, g), kMostGroups);  // its workgroups walk the list
         return LBM_OK;
     }
 

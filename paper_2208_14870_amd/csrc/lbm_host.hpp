@@ -31,6 +31,8 @@ inline unsigned blocks_for(long long n) { return (unsigned)((n + kBlock - 1) / k
 inline unsigned stride_blocks_for(long long n) {
     return (unsigned)std::min((n + kBlock - 1) / kBlock, 1LL << 23);
 }
+// The most workgroups, of up to 512 threads, of a launch over a work list.
+constexpr unsigned kMostGroups = (1u << 23) - 8;
 
 constexpr int kErrBlocks = 1024;  // grid of the two-stage FP64 reductions
 
